@@ -62,6 +62,7 @@ __device__ __forceinline__ float dpp(float v) {
 }
 constexpr int kDppQuadXor1 = 0xB1;  // quad_perm [1,0,3,2]
 constexpr int kDppQuadXor2 = 0x4E;  // quad_perm [2,3,0,1]
+constexpr int kDppQuadMirror = 0x1B;  // quad_perm [3,2,1,0]
 constexpr int kDppRowRor4 = 0x124;
 constexpr int kDppRowRor8 = 0x128;
 constexpr int kDppRowMirror = 0x140;      // lane i <- lane 15 - i of its row
@@ -102,15 +103,60 @@ __device__ __forceinline__ float quads_sum(float v) {
   return xor32_sum(xor16_sum(v));
 }
 
+// the value of lane i ^ J, in registers (a shuffle through the LDS crossbar
+// costs a round trip of 100+ clocks per step of a sort or reduction)
+template <int J>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
+  static_assert(J == 1 || J == 2 || J == 4 || J == 8 || J == 16 || J == 32, "one lane bit");
+  const int x = (int)v;
+  if constexpr (J == 1) return __builtin_amdgcn_update_dpp(0, x, kDppQuadXor1, 0xF, 0xF, false);
+  if constexpr (J == 2) return __builtin_amdgcn_update_dpp(0, x, kDppQuadXor2, 0xF, 0xF, false);
+  if constexpr (J == 4) {  // i -> 7 - i of the half row, then 3 - i of the quad
+    const int h = __builtin_amdgcn_update_dpp(0, x, kDppRowHalfMirror, 0xF, 0xF, false);
+    return __builtin_amdgcn_update_dpp(0, h, kDppQuadMirror, 0xF, 0xF, false);
+  }
+  if constexpr (J == 8) return __builtin_amdgcn_update_dpp(0, x, kDppRowRor8, 0xF, 0xF, false);
+  if constexpr (J == 16) {
+    const auto p = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    return (threadIdx.x & 16) ? p[0] : p[1];
+  }
+  if constexpr (J == 32) {
+    const auto p = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return (threadIdx.x & 32) ? p[0] : p[1];
+  }
+}
+template <int J>
+__device__ __forceinline__ float lane_xor(float v) {
+  return __uint_as_float(lane_xor<J>(__float_as_uint(v)));
+}
+template <int J>
+__device__ __forceinline__ int lane_xor(int v) {
+  return (int)lane_xor<J>((uint32_t)v);
+}
+
+// sum / max over the wave, every lane gets the result (lanes i ^ 32, 16, 8,
+// 4, 2, 1 in that order)
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-  return v;
+  v = xor16_sum(xor32_sum(v));
+  v += lane_xor<8>(v);
+  v += lane_xor<4>(v);
+  v += lane_xor<2>(v);
+  return v + lane_xor<1>(v);
 }
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, kWave));
-  return v;
+  v = xor16_max(xor32_max(v));
+  v = fmaxf(v, lane_xor<8>(v));
+  v = fmaxf(v, lane_xor<4>(v));
+  v = fmaxf(v, lane_xor<2>(v));
+  return fmaxf(v, lane_xor<1>(v));
+}
+__device__ __forceinline__ int wave_min(int v) {
+  v = min(v, lane_xor<32>(v));
+  v = min(v, lane_xor<16>(v));
+  v = min(v, lane_xor<8>(v));
+  v = min(v, lane_xor<4>(v));
+  v = min(v, lane_xor<2>(v));
+  return min(v, lane_xor<1>(v));
 }
 
 // Block-wide sum for blockDim.x == 64 * NW; every thread gets the result.

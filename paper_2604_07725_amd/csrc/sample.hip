@@ -1,10 +1,11 @@
 // Fused full-vocabulary log-softmax + Gumbel-max sampling.
 //
-// Pass 1: one 256-thread workgroup per (4096-entry vocab chunk, candidate).
-// Thread t owns the 4-entry groups 1024 r + 4 t (r < 4) of the chunk, each one
-// Philox4x32-10 counter and one 16-byte load; it computes z = logit / T, the
-// chunk-local max and sum of exp(z - max) (wavefront shuffle reductions, then
-// LDS), and the best perturbed value z + G (ties -> lowest index).  The
+// Pass 1: one 256-thread workgroup per (vocab chunk, candidate); a chunk is
+// one or more 4096-entry tiles.  Thread t owns the 4-entry groups 1024 r + 4 t
+// (r < 4) of a tile, each one Philox4x32-10 counter and one 16-byte load; it
+// computes z = logit / T, the running max and sum of exp(z - max) (reduced
+// over the wave in registers, then through LDS), and the best perturbed value
+// z + G (ties -> lowest index).  The
 // temperature mode (T = 0, T = 1, other) is a template parameter, so greedy
 // sampling carries no noise or division code.  Pass 2: one workgroup per
 // candidate merges its chunks in a fixed order and writes the token id and
@@ -16,7 +17,7 @@
 // log-probabilities under the model's own distribution (T = 1).  Pass 1 keeps
 // each chunk's conf_k largest logits (per wave by a threshold and a bitonic
 // sort, then a bitonic merge of the four waves' lists), pass 2 merges the
-// chunks' lists the same way.
+// chunks' lists the same way.  Cross-lane steps are DPP and permlane swaps.
 //
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11): 10 rounds; round r uses
 // key + r * (0x9E3779B9, 0xBB67AE85); multipliers 0xD2511F53, 0xCD9E8D57.
@@ -73,112 +74,182 @@ __device__ __forceinline__ void lse_merge(float& m, float& s, float om, float os
   m = M;
 }
 
-// The K largest of the values a wave holds (NV per lane; -inf = empty), in
-// descending order, written by lane 0 to out[0..K).  Each round takes the wave
-// maximum (ties: lowest lane, then slot) and removes it from its lane.
-template <int NV>
-__device__ __forceinline__ void wave_topk(float (&x)[NV], int K, float* out) {
-  const int lane = threadIdx.x & 63;
-  for (int r = 0; r < K; ++r) {
-    float bv = -INFINITY;
-    int bs = 0;
-#pragma unroll
-    for (int e = 0; e < NV; ++e)
-      if (x[e] > bv) {
-        bv = x[e];
-        bs = e;
-      }
-    int key = lane * NV + bs;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      const float ov = __shfl_xor(bv, o, kWave);
-      const int ok = __shfl_xor(key, o, kWave);
-      if (ov > bv || (ov == bv && ok < key)) {
-        bv = ov;
-        key = ok;
-      }
-    }
-    if (lane == key / NV) {
-      const int slot = key - (key / NV) * NV;
-#pragma unroll
-      for (int e = 0; e < NV; ++e)
-        if (e == slot) x[e] = -INFINITY;
-    }
-    if (lane == 0) out[r] = bv;
-  }
-}
+// ---- top-K lists.  An entry is a logit (the confidence) or a 64-bit key of a
+// (logit, vocab index) pair (truncated sampling); both sort descending.  All
+// cross-lane steps stay in registers (lane_xor): with shuffles through the
+// LDS crossbar the sorts and merges were most of the kernels' time.
 
-// Descending bitonic sort of one value per lane across the wave (21
-// compare-exchange steps; values only).
-__device__ __forceinline__ float wave_sort_desc(float v) {
+// Key of a (value, index) pair: larger value first, then lower index (value
+// bits made order-preserving as an unsigned word, -0 as +0, index inverted).
+typedef uint64_t pair_key;
+__device__ __forceinline__ pair_key make_key(float v, int idx) {
+  const uint32_t b = __float_as_uint(v + 0.f);
+  const uint32_t o = (b >> 31) ? ~b : b | 0x80000000u;
+  return ((pair_key)o << 32) | (uint32_t)~idx;
+}
+__device__ __forceinline__ float key_value(pair_key k) {
+  const uint32_t o = (uint32_t)(k >> 32);
+  return __uint_as_float((o >> 31) ? o & 0x7FFFFFFFu : ~o);
+}
+__device__ __forceinline__ int key_index(pair_key k) { return (int)~(uint32_t)k; }
+constexpr int kNoIndex = 0x7FFFFFFF;
+
+template <int J>
+__device__ __forceinline__ pair_key lane_xor(pair_key v) {
+  return ((pair_key)lane_xor<J>((uint32_t)(v >> 32)) << 32) | lane_xor<J>((uint32_t)v);
+}
+__device__ __forceinline__ float larger(float a, float b) { return fmaxf(a, b); }
+__device__ __forceinline__ float smaller(float a, float b) { return fminf(a, b); }
+__device__ __forceinline__ pair_key larger(pair_key a, pair_key b) { return a > b ? a : b; }
+__device__ __forceinline__ pair_key smaller(pair_key a, pair_key b) { return a > b ? b : a; }
+template <typename T>
+__device__ __forceinline__ T empty_entry();
+template <>
+__device__ __forceinline__ float empty_entry<float>() { return -INFINITY; }
+template <>
+__device__ __forceinline__ pair_key empty_entry<pair_key>() { return make_key(-INFINITY, kNoIndex); }
+__device__ __forceinline__ float entry_value(float v) { return v; }
+__device__ __forceinline__ float entry_value(pair_key k) { return key_value(k); }
+
+// Descending bitonic sort of one entry per lane (21 compare-exchange steps);
+// from K = 64 on only the last merge: a bitonic sequence into order (6 steps).
+template <int K, int J, typename T>
+__device__ __forceinline__ void sort_steps(T& v) {
   const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int k = 2; k <= 64; k <<= 1)
-#pragma unroll
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      const float o = __shfl_xor(v, j, kWave);
-      v = (((lane & k) == 0) == ((lane & j) == 0)) ? fmaxf(v, o) : fminf(v, o);
-    }
+  const T o = lane_xor<J>(v);
+  v = (((lane & K) == 0) == ((lane & J) == 0)) ? larger(v, o) : smaller(v, o);
+  if constexpr (J > 1) sort_steps<K, J / 2>(v);
+  else if constexpr (K < kWave) sort_steps<2 * K, K>(v);
+}
+template <typename T>
+__device__ __forceinline__ T wave_sort_desc(T v) {
+  sort_steps<2, 1>(v);
+  return v;
+}
+template <typename T>
+__device__ __forceinline__ T wave_merge_desc(T v) {
+  sort_steps<kWave, kWave / 2>(v);
   return v;
 }
 
-// Descending sort of a bitonic sequence held one value per lane (6 steps).
-__device__ __forceinline__ float wave_merge_desc(float v) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int j = 32; j > 0; j >>= 1) {
-    const float o = __shfl_xor(v, j, kWave);
-    v = (lane & j) == 0 ? fmaxf(v, o) : fminf(v, o);
-  }
-  return v;
+// lane i gets the entry of lane 63 - i
+template <typename T>
+__device__ __forceinline__ T lane_reverse(T v) {
+  v = lane_xor<32>(v);
+  v = lane_xor<16>(v);
+  v = lane_xor<8>(v);
+  v = lane_xor<4>(v);
+  v = lane_xor<2>(v);
+  return lane_xor<1>(v);
 }
 
-// The same result as wave_topk (the K <= 32 largest values, descending, in
-// out[0..K)), written by lanes 0..K-1, found by thresholding: L = the K-th
-// largest of the 64 lane maxima is a lower bound of the K-th largest value
-// (the K largest lane maxima are K values >= L), so the values >= L contain
-// the top K.  When there are at most 64 of them (the common case), they are
-// compacted into cand (64 floats of LDS) with ballots and sorted across the
-// wave; otherwise (many equal values, or fewer than K finite ones) the wave
-// falls back to wave_topk.  NaN is never taken, as in wave_topk.
-template <int NV>
-__device__ __forceinline__ void wave_topk_fast(float (&x)[NV], int K, float* out, float* cand) {
-  const int lane = threadIdx.x & 63;
-  float lm = -INFINITY;
-#pragma unroll
-  for (int e = 0; e < NV; ++e) lm = fmaxf(lm, x[e]);
-  const float L = __shfl(wave_sort_desc(lm), K - 1, kWave);
-  const uint64_t below = (1ull << lane) - 1ull;
+// The K <= 32 largest of the entries a wave sees, NV per lane at a time.  The
+// entries that may belong to them wait in cand (64 entries of LDS): with L a
+// lower bound of the K-th largest value, those >= L.  First bound: the K-th
+// largest of the 64 lane maxima of the first batch (the K largest lane maxima
+// are K values >= it), which leaves K to 2 K candidates of ordinary logits;
+// when the waiting ones fill up, they are sorted, the first K stay and the
+// last of these is the next bound.  A batch with more candidates than there is
+// room for (many equal values) is sorted and merged slot by slot.
+// NaN logits are empty entries, and those are never taken.
+template <typename T>
+struct TopList {
+  T* cand;
+  int K;
   int n = 0;
-#pragma unroll
-  for (int e = 0; e < NV; ++e) {
-    const bool c = x[e] >= L;
-    const uint64_t m = __ballot(c);
-    const int pos = n + __popcll(m & below);
-    if (c && pos < kWave) cand[pos] = x[e];
-    n += __popcll(m);
+  float L = -INFINITY;
+
+  // candidates in order, the first K of the wave's n kept (w: more candidates,
+  // descending, one per lane)
+  __device__ __forceinline__ T sorted(T w) {
+    const int lane = threadIdx.x & 63;
+    const T b = wave_sort_desc(lane < n ? cand[lane] : empty_entry<T>());
+    return wave_merge_desc(larger(b, lane_reverse(w)));
   }
-  if (n <= kWave) {
+  __device__ __forceinline__ T sorted() {
+    const int lane = threadIdx.x & 63;
+    return wave_sort_desc(lane < n ? cand[lane] : empty_entry<T>());
+  }
+  __device__ __forceinline__ void keep(T v) {
+    const int lane = threadIdx.x & 63;
+    if (lane < K) cand[lane] = v;
+    n = __popcll(__ballot(lane < K && v > empty_entry<T>()));
+    if (n == K) L = fmaxf(L, __shfl(entry_value(v), K - 1, kWave));
+    lds_order();
+  }
+  // the wave's LDS accesses in program order (the hardware keeps it; this
+  // holds the compiler to it)
+  __device__ __forceinline__ void lds_order() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const float v = wave_sort_desc(lane < n ? cand[lane] : -INFINITY);
-    if (lane < K) out[lane] = v;
-  } else {
-    wave_topk<NV>(x, K, out);
   }
+  template <int NV>
+  __device__ __forceinline__ void add(const T (&x)[NV], bool first) {
+    const T none = empty_entry<T>();
+    if (first) {
+      float lm = -INFINITY;
+#pragma unroll
+      for (int e = 0; e < NV; ++e) lm = fmaxf(lm, entry_value(x[e]));
+      L = __shfl(wave_sort_desc(lm), K - 1, kWave);
+    } else if (n > kWave / 2) {
+      lds_order();
+      keep(sorted());
+    }
+    const int n0 = n;
+#pragma unroll
+    for (int e = 0; e < NV; ++e) {
+      const bool c = entry_value(x[e]) >= L && x[e] > none;
+      const uint64_t m = __ballot(c);
+      if (m) {
+        const int pos = n + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                           __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+        if (c && pos < kWave) cand[pos] = x[e];
+        n += __popcll(m);
+      }
+    }
+    if (n > kWave) {
+      // no room: the batch is merged into the n0 earlier candidates slot by slot
+      n = n0;
+#pragma unroll 1
+      for (int e = 0; e < NV; ++e) {
+        T v = none;
+#pragma unroll
+        for (int j = 0; j < NV; ++j)
+          if (j == e) v = larger(x[j], none);
+        lds_order();
+        keep(sorted(wave_sort_desc(v)));
+      }
+    }
+  }
+  // the K largest, descending, to out[0..K) (empty past the last real one)
+  __device__ __forceinline__ void finish(T* out) {
+    lds_order();
+    const T v = sorted();
+    if ((threadIdx.x & 63) < K) out[threadIdx.x & 63] = v;
+  }
+};
+
+// Merges four descending lists of K <= 32 entries (list w at lists[w * 32])
+// into their K largest, descending, returned in lanes 0..K-1 (one wave).
+template <typename T>
+__device__ __forceinline__ T merge4_desc(const T* lists, int K) {
+  const int lane = threadIdx.x & 63;
+  const T none = empty_entry<T>();
+  auto get = [&](int w, int r) { return r < K ? lists[w * kConfMaxK + r] : none; };
+  // a list descending then the next ascending: a bitonic sequence
+  const T a = wave_merge_desc(lane < 32 ? get(0, lane) : get(1, 63 - lane));
+  const T b = wave_merge_desc(lane < 32 ? get(2, lane) : get(3, 63 - lane));
+  const T r = lane_reverse(b);  // (by all lanes) lanes 32..63: b[31..0], ascending
+  return wave_merge_desc(lane < 32 ? a : r);
 }
 
-// Merges four descending lists of K <= 32 values (list w at lists[w * 32])
-// into their K largest, descending, returned in lanes 0..K-1 (one wave).
-__device__ __forceinline__ float merge4_desc(const float* lists, int K) {
-  const int lane = threadIdx.x & 63;
-  auto get = [&](int w, int r) { return r < K ? lists[w * kConfMaxK + r] : -INFINITY; };
-  // list 0 descending then list 1 ascending: a bitonic sequence
-  const float a = wave_merge_desc(lane < 32 ? get(0, lane) : get(1, 63 - lane));
-  const float b = wave_merge_desc(lane < 32 ? get(2, lane) : get(3, 63 - lane));
-  const float br = __shfl(b, 63 - lane, kWave);  // lanes 32..63: b[31..0], ascending
-  return wave_merge_desc(lane < 32 ? a : br);
+// sum in order of the first n <= 64 lanes' values (uniform result)
+__device__ __forceinline__ float lanes_sum(float v, int n) {
+  float s = 0.f;
+  for (int r = 0; r < n; ++r)
+    s += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), r));
+  return s;
 }
 
 __device__ __forceinline__ bool better(float a, int ia, float b, int ib) {
@@ -186,27 +257,20 @@ __device__ __forceinline__ bool better(float a, int ia, float b, int ib) {
 }
 
 // RAW: the raw-logit statistics (m1, s1) differ from z's and are merged too;
-// otherwise they are set equal to the merged (m, s)
+// otherwise they are set equal to the merged (m, s).  Within a wave the
+// maximum is found first, so each lane rescales its sum once.
 template <int NW, bool RAW = true>
 __device__ __forceinline__ SamplePartial block_merge(SamplePartial p, SamplePartial* red) {
-  // wave level
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const float om = __shfl_xor(p.m, o, kWave);
-    const float os = __shfl_xor(p.s, o, kWave);
-    const float ob = __shfl_xor(p.best, o, kWave);
-    const int oi = __shfl_xor(p.idx, o, kWave);
-    lse_merge(p.m, p.s, om, os);
-    if constexpr (RAW) {
-      const float om1 = __shfl_xor(p.m1, o, kWave);
-      const float os1 = __shfl_xor(p.s1, o, kWave);
-      lse_merge(p.m1, p.s1, om1, os1);
-    }
-    if (better(ob, oi, p.best, p.idx)) {
-      p.best = ob;
-      p.idx = oi;
-    }
-  }
+  auto wave_lse = [](float& m, float& s) {
+    const float M = wave_max(m);
+    s = wave_sum(m == -INFINITY ? 0.f : s * exp_le0(m - M));
+    m = M;
+  };
+  wave_lse(p.m, p.s);
+  if constexpr (RAW) wave_lse(p.m1, p.s1);
+  const float B = wave_max(p.best);
+  p.idx = wave_min(p.best == B ? p.idx : kNoIndex);
+  p.best = B;
   const int w = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0) red[w] = p;
   __syncthreads();
@@ -228,23 +292,12 @@ __device__ __forceinline__ SamplePartial block_merge(SamplePartial p, SamplePart
   return r;
 }
 
-// Pass 1.  MODE 0: T = 0 (greedy, no noise, z = x); 1: T = 1 (z = x); 2: any
-// other T (z = x / T).  CONF: also the chunk's conf_k largest raw logits.
-template <int MODE, bool CONF>
-__global__ __launch_bounds__(256) void sample_partial_kernel(
-    const float* __restrict__ logits, int vocab, int64_t ld, float temp, uint64_t seed,
-    const uint64_t* __restrict__ uid, const int32_t* __restrict__ positions,
-    SamplePartial* __restrict__ part, int conf_k, float* __restrict__ topk) {
-  __shared__ SamplePartial red[4];
-  __shared__ float wtop[4][kConfMaxK];
-  __shared__ float cand[4][kWave];
-  const int chunk = blockIdx.x;
-  const int i = blockIdx.y;
-  const float* row = logits + (size_t)i * ld;
-  float raw[16];
+// the 16 logits of this thread in the 4096-entry tile at `base` (past the
+// vocabulary: -inf)
+__device__ __forceinline__ void load_tile(const float* row, int base, int vocab, float (&x)[16]) {
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const int v0 = (chunk * (kSampleChunk / 4) + r * 256 + threadIdx.x) * 4;
+    const int v0 = base + (r * 256 + threadIdx.x) * 4;
     float4 lv;
     if (v0 + 3 < vocab) {
       lv = *reinterpret_cast<const float4*>(row + v0);
@@ -254,18 +307,41 @@ __global__ __launch_bounds__(256) void sample_partial_kernel(
       lv.z = v0 + 2 < vocab ? row[v0 + 2] : -INFINITY;
       lv.w = v0 + 3 < vocab ? row[v0 + 3] : -INFINITY;
     }
-    raw[4 * r + 0] = lv.x;
-    raw[4 * r + 1] = lv.y;
-    raw[4 * r + 2] = lv.z;
-    raw[4 * r + 3] = lv.w;
+    x[4 * r + 0] = lv.x;
+    x[4 * r + 1] = lv.y;
+    x[4 * r + 2] = lv.z;
+    x[4 * r + 3] = lv.w;
   }
-  float z[16];
+}
+
+// adds 16 values to a running max and sum of exp(x - max); values without a
+// comparable one among them (all -inf or NaN) add nothing
+__device__ __forceinline__ void lse16(const float (&x)[16], float& m, float& s) {
+  float M = -INFINITY;
 #pragma unroll
-  for (int e = 0; e < 16; ++e) z[e] = MODE == 2 ? raw[e] / temp : raw[e];
-  // the best perturbed value z + G (greedy: G = 0); v ascends within a
-  // thread, so the strict > keeps the lowest index of a tie
-  float best = -INFINITY;
-  int bidx = 0x7FFFFFFF;
+  for (int e = 0; e < 16; ++e) M = fmaxf(M, x[e]);
+  if (M == -INFINITY) return;
+  M = fmaxf(M, m);
+  s = m == -INFINITY ? 0.f : s * exp_le0(m - M);
+#pragma unroll
+  for (int e = 0; e < 16; ++e) s += exp_le0(x[e] - M);  // exp(-inf) = 0
+  m = M;
+}
+
+// Pass 1.  MODE 0: T = 0 (greedy, no noise, z = x); 1: T = 1 (z = x); 2: any
+// other T (z = x / T).  CONF: also the chunk's conf_k largest raw logits.
+template <int MODE, bool CONF>
+__global__ __launch_bounds__(256) void sample_partial_kernel(
+    const float* __restrict__ logits, int vocab, int64_t ld, int tiles, float temp, uint64_t seed,
+    const uint64_t* __restrict__ uid, const int32_t* __restrict__ positions,
+    SamplePartial* __restrict__ part, int conf_k, float* __restrict__ topk) {
+  __shared__ SamplePartial red[4];
+  __shared__ float wtop[4][kConfMaxK];
+  __shared__ float cand[4][kWave];
+  const int chunk = blockIdx.x;
+  const int i = blockIdx.y;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const float* row = logits + (size_t)i * ld;
   uint64_t cu = 0;
   uint32_t pos = 0;
   if constexpr (MODE != 0) {
@@ -273,58 +349,87 @@ __global__ __launch_bounds__(256) void sample_partial_kernel(
     pos = (uint32_t)positions[i];
   }
   const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int q4 = chunk * (kSampleChunk / 4) + r * 256 + threadIdx.x;  // Philox counter word 0
-    const int v0 = q4 * 4;
-    float g[4] = {0.f, 0.f, 0.f, 0.f};
-    if constexpr (MODE != 0) {
-      if (v0 < vocab) {
-        const u32x4 w = philox4x32_10(
-            u32x4{(uint32_t)q4, pos, (uint32_t)cu, (uint32_t)(cu >> 32)}, k0, k1);
-        g[0] = gumbel_from_bits(w.x);
-        g[1] = gumbel_from_bits(w.y);
-        g[2] = gumbel_from_bits(w.z);
-        g[3] = gumbel_from_bits(w.w);
-      }
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float pv = z[4 * r + e] + g[e];
-      if (v0 + e < vocab && pv > best) {
-        best = pv;
-        bidx = v0 + e;
-      }
-    }
-  }
-  // max and sum of exp(z - max); for MODE 2 with the confidence also those
-  // of the raw logits (T = 1), else they are z's
-  auto lse16 = [](const float (&x)[16], float& m, float& s) {
-    m = -INFINITY;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) m = fmaxf(m, x[e]);
-    s = 0.f;
-    if (m != -INFINITY) {
-#pragma unroll
-      for (int e = 0; e < 16; ++e) s += exp_le0(x[e] - m);  // exp(-inf) = 0
-    }
-  };
+  // for MODE 2 with the confidence also the statistics of the raw logits
+  // (T = 1), else they are z's
   constexpr bool kRaw = MODE == 2 && CONF;
-  SamplePartial p{-INFINITY, 0.f, best, bidx, -INFINITY, 0.f};
-  lse16(z, p.m, p.s);
-  if constexpr (kRaw) lse16(raw, p.m1, p.s1);
-  p = block_merge<4, kRaw>(p, red);
-  if (threadIdx.x == 0) part[(size_t)i * gridDim.x + chunk] = p;
-  if constexpr (CONF) {
-    // the chunk's conf_k largest raw logits: per wave, then merged by wave 0
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    wave_topk_fast<16>(raw, conf_k, wtop[wave], cand[wave]);
-    __syncthreads();
-    if (wave == 0) {
-      const float v = merge4_desc(&wtop[0][0], conf_k);
-      if (lane < conf_k) topk[((size_t)i * gridDim.x + chunk) * kConfMaxK + lane] = v;
+  SamplePartial p{-INFINITY, 0.f, -INFINITY, kNoIndex, -INFINITY, 0.f};
+  TopList<float> list{cand[wave], conf_k};
+  for (int t = 0; t < tiles; ++t) {
+    const int base = (chunk * tiles + t) * kSampleChunk;
+    if (base >= vocab) break;
+    float raw[16], z[16];
+    load_tile(row, base, vocab, raw);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) z[e] = MODE == 2 ? raw[e] / temp : raw[e];
+    // the best perturbed value z + G (greedy: G = 0); v ascends within a
+    // thread, so the strict > keeps the lowest index of a tie
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int v0 = base + (r * 256 + threadIdx.x) * 4;
+      float g[4] = {0.f, 0.f, 0.f, 0.f};
+      if constexpr (MODE != 0) {
+        if (v0 < vocab) {
+          const u32x4 w = philox4x32_10(
+              u32x4{(uint32_t)v0 >> 2, pos, (uint32_t)cu, (uint32_t)(cu >> 32)}, k0, k1);
+          g[0] = gumbel_from_bits(w.x);
+          g[1] = gumbel_from_bits(w.y);
+          g[2] = gumbel_from_bits(w.z);
+          g[3] = gumbel_from_bits(w.w);
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float pv = z[4 * r + e] + g[e];
+        if (v0 + e < vocab && pv > p.best) {
+          p.best = pv;
+          p.idx = v0 + e;
+        }
+      }
+    }
+    lse16(z, p.m, p.s);
+    if constexpr (kRaw) lse16(raw, p.m1, p.s1);
+    if constexpr (CONF) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) raw[e] = raw[e] == raw[e] ? raw[e] : -INFINITY;
+      list.add(raw, t == 0);
     }
   }
+  if constexpr (CONF) list.finish(wtop[wave]);
+  p = block_merge<4, kRaw>(p, red);  // its barrier also orders the four lists
+  if (wave != 0) return;
+  if (lane == 0) part[(size_t)i * gridDim.x + chunk] = p;
+  if constexpr (CONF) {
+    const float v = merge4_desc(&wtop[0][0], conf_k);
+    if (lane < conf_k) topk[((size_t)i * gridDim.x + chunk) * kConfMaxK + lane] = v;
+  }
+}
+
+// Loads a wave's share of a row's chunk lists (nchunks lists of L entries at
+// stride kConfMaxK, flattened; wave w takes a contiguous quarter) and leaves
+// the share's L largest in out: NV * 64 entries per wave at most.
+template <int NV, typename T, typename Get>
+__device__ __forceinline__ void merge_share(int nchunks, int L, Get get, T* out, T* cand) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int total = nchunks * L, per = (total + 3) / 4;
+  T x[NV];
+#pragma unroll
+  for (int e = 0; e < NV; ++e) {
+    const int q = wave * per + e * kWave + lane;  // entry of the flattened lists
+    const bool ok = e * kWave + lane < per && q < total;
+    const int c = ok ? q / L : 0;
+    x[e] = ok ? get((size_t)c * kConfMaxK + (q - c * L)) : empty_entry<T>();
+  }
+  TopList<T> list{cand, L};
+  list.add(x, true);
+  list.finish(out);
+}
+// up to kConfSmallNV * 256 entries (a 152K vocabulary at L <= 26) take the
+// short form: the general one walks 24 mostly empty slots per lane
+constexpr int kConfSmallNV = 4;
+template <typename T, typename Get>
+__device__ __forceinline__ void merge_lists(int nchunks, int L, Get get, T* out, T* cand) {
+  if (nchunks * L <= kConfSmallNV * 4 * kWave) merge_share<kConfSmallNV>(nchunks, L, get, out, cand);
+  else merge_share<kConfMergeNV>(nchunks, L, get, out, cand);
 }
 
 __global__ __launch_bounds__(256) void sample_final_kernel(
@@ -334,8 +439,9 @@ __global__ __launch_bounds__(256) void sample_final_kernel(
     float* __restrict__ conf_sum) {
   __shared__ SamplePartial red[4];
   __shared__ float wtop[4][kConfMaxK];
+  __shared__ float cand[4][kWave];
   const int i = blockIdx.x;
-  SamplePartial p{-INFINITY, 0.f, -INFINITY, 0x7FFFFFFF, -INFINITY, 0.f};
+  SamplePartial p{-INFINITY, 0.f, -INFINITY, kNoIndex, -INFINITY, 0.f};
   for (int c = threadIdx.x; c < nchunks; c += 256) {
     const SamplePartial o = part[(size_t)i * nchunks + c];
     lse_merge(p.m, p.s, o.m, o.s);
@@ -345,8 +451,16 @@ __global__ __launch_bounds__(256) void sample_final_kernel(
       p.idx = o.idx;
     }
   }
-  p = block_merge<4>(p, red);
-  if (threadIdx.x == 0) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  if (conf_k > 0) {
+    // merge the chunks' lists: a quarter per wave, then wave 0 merges the four
+    // results (host checks nchunks * conf_k fits)
+    const float* src = topk + (size_t)i * nchunks * kConfMaxK;
+    merge_lists(nchunks, conf_k, [&](size_t o) { return src[o]; }, wtop[wave], cand[wave]);
+  }
+  p = block_merge<4>(p, red);  // its barrier also orders the four lists
+  if (wave != 0) return;
+  if (lane == 0) {
     const int id = p.idx;
     if (id < 0 || id >= vocab) {
       // no perturbed value compared greater than -inf (every logit NaN): no
@@ -361,38 +475,11 @@ __global__ __launch_bounds__(256) void sample_final_kernel(
     }
   }
   if (conf_k > 0) {
-    // merge the chunks' lists: wave w takes a contiguous quarter of them (entry
-    // wave * per + 64 e + lane in lane, slot e), then wave 0 merges the four
-    // results (host checks nchunks * conf_k fits)
-    __shared__ float cand[4][kWave];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int total = nchunks * conf_k;
-    const int per = (total + 3) / 4;
-    const float* src = topk + (size_t)i * nchunks * kConfMaxK;
-    float x[kConfMergeNV];
-#pragma unroll
-    for (int e = 0; e < kConfMergeNV; ++e) {
-      const int q = wave * per + e * kWave + lane;  // entry of the flattened lists
-      const bool ok = e * kWave + lane < per && q < total;
-      const int c = ok ? q / conf_k : 0;
-      x[e] = ok ? src[(size_t)c * kConfMaxK + (q - c * conf_k)] : -INFINITY;
-    }
-    wave_topk_fast<kConfMergeNV>(x, conf_k, wtop[wave], cand[wave]);
-    __syncthreads();
-    if (wave == 0) {
-      __shared__ float top[kConfMaxK];
-      const float v = merge4_desc(&wtop[0][0], conf_k);
-      if (lane < conf_k) top[lane] = v;
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      if (lane == 0) {
-        float sum = 0.f;
-        for (int r = 0; r < conf_k; ++r) sum += top[r];
-        const float c = (p.m1 + logf(p.s1)) - sum / (float)conf_k;
-        if (out_conf) out_conf[i] = c;
-        if (conf_sum) conf_sum[i] += c;
-      }
+    const float sum = lanes_sum(merge4_desc(&wtop[0][0], conf_k), conf_k);
+    if (lane == 0) {
+      const float c = (p.m1 + logf(p.s1)) - sum / (float)conf_k;
+      if (out_conf) out_conf[i] = c;
+      if (conf_sum) conf_sum[i] += c;
     }
   }
 }
@@ -420,104 +507,42 @@ __global__ __launch_bounds__(256) void group_confidence_kernel(
 // top_p.  The token is the Gumbel-max over the kept entries (same Philox noise
 // as the full sampler), lp = z_id - logsumexp(kept z).  T = 0: the first entry,
 // with the truncation and lp evaluated at T = 1.
-__device__ __forceinline__ bool pair_before(float a, int ia, float b, int ib) {
-  return a > b || (a == b && ia < ib);
-}
-
-// The K first (value, index) pairs of a wave in pair_before order (NV per
-// lane; empty = (-inf, INT_MAX)), written by lane 0 to out_v / out_i.
-template <int NV>
-__device__ __forceinline__ void wave_topk_pairs(float (&x)[NV], int (&xi)[NV], int K, float* out_v,
-                                                int* out_i) {
-  const int lane = threadIdx.x & 63;
-  for (int r = 0; r < K; ++r) {
-    float bv = -INFINITY;
-    int bi = 0x7FFFFFFF;
-#pragma unroll
-    for (int e = 0; e < NV; ++e)
-      if (pair_before(x[e], xi[e], bv, bi)) {
-        bv = x[e];
-        bi = xi[e];
-      }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      const float ov = __shfl_xor(bv, o, kWave);
-      const int oi = __shfl_xor(bi, o, kWave);
-      if (pair_before(ov, oi, bv, bi)) {
-        bv = ov;
-        bi = oi;
-      }
-    }
-    // vocab indices are unique: exactly one slot holds a real winner
-#pragma unroll
-    for (int e = 0; e < NV; ++e)
-      if (xi[e] == bi && x[e] == bv) {
-        x[e] = -INFINITY;
-        xi[e] = 0x7FFFFFFF;
-      }
-    if (lane == 0) {
-      out_v[r] = bv;
-      out_i[r] = bi;
-    }
-  }
-}
-
 __global__ __launch_bounds__(256) void sample_trunc_partial_kernel(
-    const float* __restrict__ logits, int vocab, int64_t ld, int L, SamplePartial* __restrict__ part,
-    float* __restrict__ topv, int* __restrict__ topi) {
+    const float* __restrict__ logits, int vocab, int64_t ld, int tiles, int L,
+    SamplePartial* __restrict__ part, float* __restrict__ topv, int* __restrict__ topi) {
   __shared__ SamplePartial red[4];
-  __shared__ float wv[4][kConfMaxK];
-  __shared__ int wi[4][kConfMaxK];
+  __shared__ pair_key wtop[4][kConfMaxK];
+  __shared__ pair_key cand[4][kWave];
   const int chunk = blockIdx.x;
   const int i = blockIdx.y;
-  const float* row = logits + (size_t)i * ld;
-  float x[16];
-  int xi[16];
-  float m1 = -INFINITY;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int v0 = (chunk * (kSampleChunk / 4) + r * 256 + threadIdx.x) * 4;
-    float4 lv;
-    if (v0 + 3 < vocab) {
-      lv = *reinterpret_cast<const float4*>(row + v0);
-    } else {
-      lv.x = v0 + 0 < vocab ? row[v0 + 0] : -INFINITY;
-      lv.y = v0 + 1 < vocab ? row[v0 + 1] : -INFINITY;
-      lv.z = v0 + 2 < vocab ? row[v0 + 2] : -INFINITY;
-      lv.w = v0 + 3 < vocab ? row[v0 + 3] : -INFINITY;
-    }
-    const float vals[4] = {lv.x, lv.y, lv.z, lv.w};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      x[r * 4 + e] = vals[e];
-      xi[r * 4 + e] = v0 + e < vocab ? v0 + e : 0x7FFFFFFF;
-      m1 = fmaxf(m1, vals[e]);
-    }
-  }
-  float s1 = 0.f;
-  if (m1 != -INFINITY) {
-#pragma unroll
-    for (int e = 0; e < 16; ++e) s1 += (x[e] == -INFINITY) ? 0.f : expf(x[e] - m1);
-  }
-  SamplePartial p{m1, s1, -INFINITY, 0x7FFFFFFF, m1, s1};
-  p = block_merge<4>(p, red);
-  if (threadIdx.x == 0) part[(size_t)i * gridDim.x + chunk] = p;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  wave_topk_pairs<16>(x, xi, L, wv[wave], wi[wave]);
-  __syncthreads();
-  if (wave == 0) {
-    float x2[2];
-    int i2[2];
+  const float* row = logits + (size_t)i * ld;
+  SamplePartial p{-INFINITY, 0.f, -INFINITY, kNoIndex, -INFINITY, 0.f};
+  TopList<pair_key> list{cand[wave], L};
+  for (int t = 0; t < tiles; ++t) {
+    const int base = (chunk * tiles + t) * kSampleChunk;
+    if (base >= vocab) break;
+    float x[16];
+    load_tile(row, base, vocab, x);
+    lse16(x, p.m, p.s);
+    pair_key key[16];
 #pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const int q = lane * 2 + e;
-      const int w = q / kConfMaxK, r = q - w * kConfMaxK;
-      const bool ok = w < 4 && r < L;
-      x2[e] = ok ? wv[w][r] : -INFINITY;
-      i2[e] = ok ? wi[w][r] : 0x7FFFFFFF;
+    for (int e = 0; e < 16; ++e) {
+      // past the vocabulary or NaN: empty (a -inf logit is an entry)
+      const int v = base + ((e >> 2) * 256 + threadIdx.x) * 4 + (e & 3);
+      key[e] = v < vocab && x[e] == x[e] ? make_key(x[e], v) : empty_entry<pair_key>();
     }
-    const size_t o = ((size_t)i * gridDim.x + chunk) * kConfMaxK;
-    wave_topk_pairs<2>(x2, i2, L, topv + o, topi + o);
+    list.add(key, t == 0);
+  }
+  list.finish(wtop[wave]);
+  p = block_merge<4, false>(p, red);  // its barrier also orders the four lists
+  if (wave != 0) return;
+  if (lane == 0) part[(size_t)i * gridDim.x + chunk] = p;
+  const pair_key k = merge4_desc(&wtop[0][0], L);
+  const size_t o = ((size_t)i * gridDim.x + chunk) * kConfMaxK;
+  if (lane < L) {
+    topv[o + lane] = key_value(k);
+    topi[o + lane] = key_index(k);
   }
 }
 
@@ -528,122 +553,87 @@ __global__ __launch_bounds__(256) void sample_trunc_final_kernel(
     int32_t* __restrict__ out_tokens, float* __restrict__ out_lp, int conf_k,
     float* __restrict__ out_conf, float* __restrict__ conf_sum) {
   __shared__ SamplePartial red[4];
-  __shared__ float wv[4][kConfMaxK];
-  __shared__ int wi[4][kConfMaxK];
-  __shared__ float fv[kConfMaxK];
-  __shared__ int fi[kConfMaxK];
-  __shared__ int keep[kConfMaxK];
+  __shared__ pair_key wtop[4][kConfMaxK];
+  __shared__ pair_key cand[4][kWave];
   const int i = blockIdx.x;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   // logsumexp of the raw logits (confidence)
-  SamplePartial p{-INFINITY, 0.f, -INFINITY, 0x7FFFFFFF, -INFINITY, 0.f};
+  SamplePartial p{-INFINITY, 0.f, -INFINITY, kNoIndex, -INFINITY, 0.f};
   for (int c = threadIdx.x; c < nchunks; c += 256) {
     const SamplePartial o = part[(size_t)i * nchunks + c];
-    lse_merge(p.m1, p.s1, o.m1, o.s1);
+    lse_merge(p.m, p.s, o.m, o.s);
   }
-  p.m = p.m1;
-  p.s = p.s1;
-  p = block_merge<4>(p, red);
   // merge the chunks' lists: a quarter per wave, then wave 0 merges the four
-  const int total = nchunks * L;
-  const int per = (total + 3) / 4;
   const size_t base = (size_t)i * nchunks * kConfMaxK;
-  float x[kConfMergeNV];
-  int xi[kConfMergeNV];
-#pragma unroll
-  for (int e = 0; e < kConfMergeNV; ++e) {
-    const int q = wave * per + lane * kConfMergeNV + e;
-    const bool ok = lane * kConfMergeNV + e < per && q < total;
-    const int c = ok ? q / L : 0;
-    x[e] = ok ? topv[base + (size_t)c * kConfMaxK + (q - c * L)] : -INFINITY;
-    xi[e] = ok ? topi[base + (size_t)c * kConfMaxK + (q - c * L)] : 0x7FFFFFFF;
-  }
-  wave_topk_pairs<kConfMergeNV>(x, xi, L, wv[wave], wi[wave]);
-  __syncthreads();
+  merge_lists(nchunks, L, [&](size_t o) { return make_key(topv[base + o], topi[base + o]); },
+              wtop[wave], cand[wave]);
+  p = block_merge<4, false>(p, red);  // its barrier also orders the four lists
   if (wave != 0) return;
-  {
-    float x2[2];
-    int i2[2];
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const int q = lane * 2 + e;
-      const int w = q / kConfMaxK, r = q - w * kConfMaxK;
-      const bool ok = w < 4 && r < L;
-      x2[e] = ok ? wv[w][r] : -INFINITY;
-      i2[e] = ok ? wi[w][r] : 0x7FFFFFFF;
-    }
-    wave_topk_pairs<2>(x2, i2, L, fv, fi);
-  }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  // lane j < L holds entry j of the row's list
+  const pair_key k = merge4_desc(&wtop[0][0], L);
+  const float fv = key_value(k);
+  const int fi = key_index(k);
   const float tdiv = temp == 0.f ? 1.f : temp;  // T = 0: truncation and lp at T = 1
-  if (lane == 0) {
-    // min-p, then top-p in list order over the renormalised min-p set
-    const float z0 = fv[0] / tdiv;
-    float tot = 0.f;
-    for (int j = 0; j < top_k; ++j) {
-      const float d = fv[j] / tdiv - z0;
-      const bool k = !(min_p > 0.f) || d >= logf(min_p);
-      keep[j] = k;
-      if (k) tot += expf(d);
-    }
-    if (top_p < 1.f) {
-      float cum = 0.f;
-      for (int j = 0; j < top_k; ++j) {
-        if (!keep[j]) continue;
-        if (!(cum < top_p * tot)) keep[j] = 0;
-        else cum += expf(fv[j] / tdiv - z0);
-      }
+  const float z = fv / tdiv;
+  const float z0 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(z)));
+  // min-p, then top-p in list order over the renormalised min-p set
+  const float d = z - z0;
+  bool keep = lane < top_k && (!(min_p > 0.f) || d >= logf(min_p));
+  const float ez = expf(d);
+  const float et = keep ? ez : 0.f;
+  if (top_p < 1.f) {
+    const float bound = top_p * lanes_sum(et, top_k);
+    float cum = 0.f;
+    for (int j = 0; j < top_k; ++j) {  // the probability before entry j, in list order
+      if (lane == j && !(cum < bound)) keep = false;
+      const float w = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(et), j));
+      if (cum < bound) cum += w;
     }
   }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  // Gumbel-max over the kept entries (lane j holds entry j)
-  float pv = -INFINITY, ez = 0.f;
-  int pid = 0x7FFFFFFF;
-  if (lane < top_k && keep[lane]) {
-    const int v = fi[lane];
-    const float z = fv[lane] / tdiv;
-    ez = expf(z - fv[0] / tdiv);
+  // Gumbel-max over the kept entries
+  float pv = -INFINITY;
+  int pid = kNoIndex;
+  if (keep) {
     float g = 0.f;
     if (temp != 0.f) {
       const uint64_t cu = uid[i];
       const u32x4 w = philox4x32_10(
-          u32x4{(uint32_t)(v >> 2), (uint32_t)positions[i], (uint32_t)cu, (uint32_t)(cu >> 32)},
+          u32x4{(uint32_t)(fi >> 2), (uint32_t)positions[i], (uint32_t)cu, (uint32_t)(cu >> 32)},
           (uint32_t)seed, (uint32_t)(seed >> 32));
-      const uint32_t word = (v & 3) == 0 ? w.x : (v & 3) == 1 ? w.y : (v & 3) == 2 ? w.z : w.w;
+      const uint32_t word = (fi & 3) == 0 ? w.x : (fi & 3) == 1 ? w.y : (fi & 3) == 2 ? w.z : w.w;
       g = gumbel_from_bits(word);
     }
     pv = z + g;
-    pid = v;
+    pid = fi;
   }
-  float zme = (lane < top_k && keep[lane]) ? fv[lane] / tdiv : -INFINITY;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const float ov = __shfl_xor(pv, o, kWave);
-    const int oi = __shfl_xor(pid, o, kWave);
-    const float oz = __shfl_xor(zme, o, kWave);
-    if (pair_before(ov, oi, pv, pid)) {
-      pv = ov;
-      pid = oi;
-      zme = oz;
-    }
-    ez += __shfl_xor(ez, o, kWave);
+  const float sum_ez = wave_sum(keep ? ez : 0.f);
+  const float best = wave_max(pv);
+  const int id = wave_min(pv == best ? pid : kNoIndex);
+  const bool found = id >= 0 && id != kNoIndex;  // a kept entry won
+  if (lane == 0 && !found) {
+    out_tokens[i] = -1;
+    out_lp[i] = __builtin_nanf("");
   }
-  if (lane == 0) {
-    const bool found = pid >= 0 && pid != 0x7FFFFFFF;   // a kept entry won
-    out_tokens[i] = found ? pid : -1;
-    out_lp[i] = found ? zme - (fv[0] / tdiv + logf(ez)) : __builtin_nanf("");
-    if (conf_k > 0) {
-      float sum = 0.f;
-      for (int r = 0; r < conf_k; ++r) sum += fv[r];
-      const float c = (p.m1 + logf(p.s1)) - sum / (float)conf_k;
+  if (found && keep && fi == id) {  // the winner's lane (indices are unique)
+    out_tokens[i] = id;
+    out_lp[i] = z - (z0 + logf(sum_ez));
+  }
+  if (conf_k > 0) {
+    const float sum = lanes_sum(fv, conf_k);
+    if (lane == 0) {
+      const float c = (p.m + logf(p.s)) - sum / (float)conf_k;
       if (out_conf) out_conf[i] = c;
       if (conf_sum) conf_sum[i] += c;
     }
   }
+}
+
+// 4096-entry tiles per workgroup: one while that is needed to fill the chip;
+// from kTiledGroups workgroups of four on, four, so that a wave sorts and a
+// workgroup merges its list once per 16384 entries.
+constexpr int kTiledGroups = 2048;
+static int sample_tiles(int n, int vocab) {
+  return (long long)n * ((vocab + 4 * kSampleChunk - 1) / (4 * kSampleChunk)) >= kTiledGroups ? 4 : 1;
 }
 
 static size_t partial_bytes(int n, int nchunks) {
@@ -671,7 +661,8 @@ hipError_t launch_logprob_sample(const float* logits, int n, int vocab, int64_t 
                                  int conf_k, float* out_conf, float* conf_sum, hipStream_t st,
                                  int top_k, float top_p, float min_p) {
   if (n == 0) return hipSuccess;
-  const int nchunks = (vocab + kSampleChunk - 1) / kSampleChunk;
+  const int tiles = sample_tiles(n, vocab);
+  const int nchunks = (vocab + tiles * kSampleChunk - 1) / (tiles * kSampleChunk);
   SamplePartial* part = reinterpret_cast<SamplePartial*>(workspace);
   char* lists = reinterpret_cast<char*>(workspace) + partial_bytes(n, nchunks);
   float* topk = reinterpret_cast<float*>(lists);
@@ -679,7 +670,7 @@ hipError_t launch_logprob_sample(const float* logits, int n, int vocab, int64_t 
   if (top_k > 0) {
     const int L = top_k > conf_k ? top_k : conf_k;
     hipLaunchKernelGGL(sample_trunc_partial_kernel, dim3(nchunks, n), dim3(256), 0, st, logits,
-                       vocab, ld, L, part, topk, topi);
+                       vocab, ld, tiles, L, part, topk, topi);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(sample_trunc_final_kernel, dim3(n), dim3(256), 0, st, part, nchunks, L,
@@ -687,7 +678,7 @@ hipError_t launch_logprob_sample(const float* logits, int n, int vocab, int64_t 
                        out_lp, conf_k, out_conf, conf_sum);
     return hipGetLastError();
   }
-  using PartialFn = void (*)(const float*, int, int64_t, float, uint64_t, const uint64_t*,
+  using PartialFn = void (*)(const float*, int, int64_t, int, float, uint64_t, const uint64_t*,
                             const int32_t*, SamplePartial*, int, float*);
   static constexpr PartialFn kPartial[3][2] = {
       {sample_partial_kernel<0, false>, sample_partial_kernel<0, true>},
@@ -695,7 +686,7 @@ hipError_t launch_logprob_sample(const float* logits, int n, int vocab, int64_t 
       {sample_partial_kernel<2, false>, sample_partial_kernel<2, true>}};
   const int mode = temp == 0.f ? 0 : temp == 1.f ? 1 : 2;
   hipLaunchKernelGGL(kPartial[mode][conf_k > 0 ? 1 : 0], dim3(nchunks, n), dim3(256), 0, st,
-                     logits, vocab, ld, temp, seed, uid, positions, part, conf_k, topk);
+                     logits, vocab, ld, tiles, temp, seed, uid, positions, part, conf_k, topk);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(sample_final_kernel, dim3(n), dim3(256), 0, st, part, nchunks, logits, vocab,

@@ -427,6 +427,51 @@ def test_self_confidence_ties_and_uniform(S):
     assert abs(float(conf[0]) - np.log(vocab)) < 2e-5
 
 
+@pytest.mark.parametrize("n,vocab", [
+    (4, 4096 + 12),      # a last tile of three lanes
+    (3, 33),             # one tile, fewer lanes than entries kept
+    (2, 160),            # one wave's lanes partly used, more than 64 entries
+    (260, 4 * 16384 - 4 * 4096 + 64)])  # four tiles per workgroup, the last one short
+@pytest.mark.parametrize("k", [1, 32])
+def test_sampler_lists_at_tile_and_list_edges(S, n, vocab, k):
+    """Top-k lists where their selection changes form: rows with fewer finite
+    logits than k (the rest -inf), runs of equal logits longer than a list's
+    buffer (in the first tile and in a later one), ordinary rows; full
+    sampling with the confidence and truncated sampling, against the oracle."""
+    sevo, _ = S
+    say(f"sampler lists n={n} vocab={vocab} k={k}")
+    n0 = n
+    n = min(n, 4)                      # distinct rows; the rest repeat them
+    host, _ = _logits(n, vocab, vocab, 5)
+    host[0, :] = -np.inf
+    host[0, vocab // 3:vocab // 3 + 9] = np.arange(9) % 4          # 9 finite logits, ties
+    host[1, vocab // 2:vocab // 2 + 200] = 6.5                     # up to 200 equal maxima
+    rep = np.arange(n0) % n
+    dev = torch.zeros(n0, -(-vocab // 4) * 4, dtype=torch.float32, device="cuda")
+    dev[:, :vocab] = torch.from_numpy(host[rep]).cuda()
+    uid = torch.from_numpy((rep * 31 + 7).astype(np.int64)).cuda()
+    pos = torch.from_numpy((rep * 5 + 1).astype(np.int32)).cuda()
+    ws = poisoned(sevo.sevo_sample_workspace_bytes(n0, vocab))
+    kc = min(k, 9)                     # the confidence of fewer than k finite logits is infinite
+    _, lp, conf = sevo.sevo_logprob_sample(dev, 1.0, 3, uid, pos, vocab=vocab, conf_topk=kc,
+                                           workspace=ws)
+    ids, lps = sevo.sevo_logprob_sample(dev, 1.0, 3, uid, pos, vocab=vocab, top_k=min(k, vocab),
+                                        workspace=ws)
+    torch.cuda.synchronize()
+    ref = od.token_confidence(host.astype(np.float64), kc)
+    # fp32 logsumexp of values up to 6.5: a few units of 2^-21
+    assert np.abs(conf.cpu().numpy() - ref[rep]).max() <= 2e-5
+    assert np.isfinite(lp.cpu().numpy()).all()
+    det = {}
+    with np.errstate(invalid="ignore", divide="ignore"):
+        rid, rlp, gap = od.truncated_logprob_sample(host, 1.0, 3, np.arange(n) * 31 + 7,
+                                                    np.arange(n) * 5 + 1, min(k, vocab),
+                                                    details=det)
+    got = ids.cpu().numpy()
+    np.testing.assert_array_equal(got, got[:n][rep])
+    check_ids(got[:n], lps.cpu().numpy()[:n], rid, rlp, gap, det, label="lists")
+
+
 def test_group_confidence_matches_oracle(S):
     sevo, _ = S
     rng = np.random.default_rng(3)
