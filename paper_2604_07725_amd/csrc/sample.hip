@@ -23,6 +23,8 @@
 // key + r * (0x9E3779B9, 0xBB67AE85); multipliers 0xD2511F53, 0xCD9E8D57.
 // Counter (v >> 2, position, uid lo, uid hi), key (seed lo, seed hi), word v & 3.
 // u = ((w >> 9) + 0.5) 2^-23 (exact in fp32), G = -log(-log u).
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -110,6 +112,12 @@ template <>
 __device__ __forceinline__ pair_key empty_entry<pair_key>() { return make_key(-INFINITY, kNoIndex); }
 __device__ __forceinline__ float entry_value(float v) { return v; }
 __device__ __forceinline__ float entry_value(pair_key k) { return key_value(k); }
+// the smallest entry of a value >= L that is not empty: one compare then tests
+// both (a NaN logit fails it)
+__device__ __forceinline__ float lowest_at(float L, float) { return fmaxf(L, -3.402823466e38f); }
+__device__ __forceinline__ pair_key lowest_at(float L, pair_key none) {
+  return larger(make_key(L, -1), none + 1);
+}
 
 // Descending bitonic sort of one entry per lane (21 compare-exchange steps);
 // from K = 64 on only the last merge: a bitonic sequence into order (6 steps).
@@ -150,7 +158,10 @@ __device__ __forceinline__ T lane_reverse(T v) {
 // are K values >= it), which leaves K to 2 K candidates of ordinary logits;
 // when the waiting ones fill up, they are sorted, the first K stay and the
 // last of these is the next bound.  A batch with more candidates than there is
-// room for (many equal values) is sorted and merged slot by slot.
+// room for (many equal values) is sorted and merged slot by slot.  K rounds of
+// a wave arg-max through LDS shuffles were latency-bound: 45 + 55 us for top-k
+// 20 over 16 x 151936 logits, 11 + 9 us so; a step's final merge with the
+// confidence at a vocabulary of 4096 26.6 -> 5.2 us.
 // NaN logits are empty entries, and those are never taken.
 template <typename T>
 struct TopList {
@@ -184,23 +195,24 @@ struct TopList {
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
+  // lm: the largest of the lane's values
   template <int NV>
-  __device__ __forceinline__ void add(const T (&x)[NV], bool first) {
+  __device__ __forceinline__ void add(const T (&x)[NV], float lm, bool first) {
     const T none = empty_entry<T>();
     if (first) {
-      float lm = -INFINITY;
-#pragma unroll
-      for (int e = 0; e < NV; ++e) lm = fmaxf(lm, entry_value(x[e]));
       L = __shfl(wave_sort_desc(lm), K - 1, kWave);
+    } else if (!__any(lm >= L)) {
+      return;
     } else if (n > kWave / 2) {
       lds_order();
       keep(sorted());
     }
     const int n0 = n;
+    const T low = lowest_at(L, none);
 #pragma unroll
     for (int e = 0; e < NV; ++e) {
-      const bool c = entry_value(x[e]) >= L && x[e] > none;
-      const uint64_t m = __ballot(c);
+      const bool c = x[e] >= low;
+      const uint64_t m = __builtin_amdgcn_ballot_w64(c);
       if (m) {
         const int pos = n + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
@@ -292,36 +304,50 @@ __device__ __forceinline__ SamplePartial block_merge(SamplePartial p, SamplePart
   return r;
 }
 
-// the 16 logits of this thread in the 4096-entry tile at `base` (past the
-// vocabulary: -inf)
+// The 16 logits of this thread in the 4096-entry tile at `base` (past the
+// vocabulary: -inf).  The four 16-byte loads are issued without a branch
+// between them: with the guarded scalar loads of the vocabulary's end in the
+// way, each waited for the one before it (scored rows of 152K logits with the
+// confidence: 2.8 TB/s).  A group past the end reads the row's first one.
 __device__ __forceinline__ void load_tile(const float* row, int base, int vocab, float (&x)[16]) {
+  const int v0 = base + threadIdx.x * 4;
+  if (base + kSampleChunk <= vocab) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float4 lv = *reinterpret_cast<const float4*>(row + v0 + 1024 * r);
+      x[4 * r] = lv.x, x[4 * r + 1] = lv.y, x[4 * r + 2] = lv.z, x[4 * r + 3] = lv.w;
+    }
+    return;
+  }
+  if (vocab >= 4) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int v = v0 + 1024 * r;
+      const float4 lv = *reinterpret_cast<const float4*>(row + (v + 3 < vocab ? v : 0));
+      x[4 * r] = lv.x, x[4 * r + 1] = lv.y, x[4 * r + 2] = lv.z, x[4 * r + 3] = lv.w;
+    }
+  }
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const int v0 = base + (r * 256 + threadIdx.x) * 4;
-    float4 lv;
-    if (v0 + 3 < vocab) {
-      lv = *reinterpret_cast<const float4*>(row + v0);
-    } else {
-      lv.x = v0 + 0 < vocab ? row[v0 + 0] : -INFINITY;
-      lv.y = v0 + 1 < vocab ? row[v0 + 1] : -INFINITY;
-      lv.z = v0 + 2 < vocab ? row[v0 + 2] : -INFINITY;
-      lv.w = v0 + 3 < vocab ? row[v0 + 3] : -INFINITY;
-    }
-    x[4 * r + 0] = lv.x;
-    x[4 * r + 1] = lv.y;
-    x[4 * r + 2] = lv.z;
-    x[4 * r + 3] = lv.w;
+    const int v = v0 + 1024 * r;
+    if (v + 3 < vocab) continue;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[4 * r + e] = v + e < vocab ? row[v + e] : -INFINITY;
   }
 }
 
-// adds 16 values to a running max and sum of exp(x - max); values without a
-// comparable one among them (all -inf or NaN) add nothing
-__device__ __forceinline__ void lse16(const float (&x)[16], float& m, float& s) {
-  float M = -INFINITY;
+__device__ __forceinline__ float max16(const float (&x)[16]) {
+  float t = -INFINITY;
 #pragma unroll
-  for (int e = 0; e < 16; ++e) M = fmaxf(M, x[e]);
-  if (M == -INFINITY) return;
-  M = fmaxf(M, m);
+  for (int e = 0; e < 16; ++e) t = fmaxf(t, x[e]);
+  return t;
+}
+
+// adds 16 values, t their largest, to a running max and sum of exp(x - max);
+// values without a comparable one among them (all -inf or NaN) add nothing
+__device__ __forceinline__ void lse16(const float (&x)[16], float t, float& m, float& s) {
+  if (t == -INFINITY) return;
+  const float M = fmaxf(m, t);
   s = m == -INFINITY ? 0.f : s * exp_le0(m - M);
 #pragma unroll
   for (int e = 0; e < 16; ++e) s += exp_le0(x[e] - M);  // exp(-inf) = 0
@@ -354,20 +380,32 @@ __global__ __launch_bounds__(256) void sample_partial_kernel(
   constexpr bool kRaw = MODE == 2 && CONF;
   SamplePartial p{-INFINITY, 0.f, -INFINITY, kNoIndex, -INFINITY, 0.f};
   TopList<float> list{cand[wave], conf_k};
+  int best_base = 0;  // MODE 0: the tile of this lane's first largest value
+  float next[16];
+  load_tile(row, chunk * tiles * kSampleChunk, vocab, next);
   for (int t = 0; t < tiles; ++t) {
     const int base = (chunk * tiles + t) * kSampleChunk;
     if (base >= vocab) break;
     float raw[16], z[16];
-    load_tile(row, base, vocab, raw);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) raw[e] = next[e];
+    if (t + 1 < tiles && base + kSampleChunk < vocab)
+      load_tile(row, base + kSampleChunk, vocab, next);
 #pragma unroll
     for (int e = 0; e < 16; ++e) z[e] = MODE == 2 ? raw[e] / temp : raw[e];
-    // the best perturbed value z + G (greedy: G = 0); v ascends within a
-    // thread, so the strict > keeps the lowest index of a tie
+    const float zmax = max16(z);
+    if constexpr (MODE == 0) {
+      if (zmax > p.best) {
+        p.best = zmax;
+        best_base = base;
+      }
+    } else {
+      // the best perturbed value z + G; v ascends within a thread, so the
+      // strict > keeps the lowest index of a tie
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int v0 = base + (r * 256 + threadIdx.x) * 4;
-      float g[4] = {0.f, 0.f, 0.f, 0.f};
-      if constexpr (MODE != 0) {
+      for (int r = 0; r < 4; ++r) {
+        const int v0 = base + (r * 256 + threadIdx.x) * 4;
+        float g[4] = {0.f, 0.f, 0.f, 0.f};
         if (v0 < vocab) {
           const u32x4 w = philox4x32_10(
               u32x4{(uint32_t)v0 >> 2, pos, (uint32_t)cu, (uint32_t)(cu >> 32)}, k0, k1);
@@ -376,22 +414,28 @@ __global__ __launch_bounds__(256) void sample_partial_kernel(
           g[2] = gumbel_from_bits(w.z);
           g[3] = gumbel_from_bits(w.w);
         }
-      }
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float pv = z[4 * r + e] + g[e];
-        if (v0 + e < vocab && pv > p.best) {
-          p.best = pv;
-          p.idx = v0 + e;
+        for (int e = 0; e < 4; ++e) {
+          const float pv = z[4 * r + e] + g[e];
+          if (v0 + e < vocab && pv > p.best) {
+            p.best = pv;
+            p.idx = v0 + e;
+          }
         }
       }
     }
-    lse16(z, p.m, p.s);
-    if constexpr (kRaw) lse16(raw, p.m1, p.s1);
-    if constexpr (CONF) {
+    lse16(z, zmax, p.m, p.s);
+    const float rmax = kRaw ? max16(raw) : zmax;
+    if constexpr (kRaw) lse16(raw, rmax, p.m1, p.s1);
+    if constexpr (CONF) list.add(raw, rmax, t == 0);
+  }
+  if constexpr (MODE == 0) {
+    // the index of the largest value: its first place in the lane's tile
+    if (p.best > -INFINITY) {
+      if (tiles > 1) load_tile(row, best_base, vocab, next);
 #pragma unroll
-      for (int e = 0; e < 16; ++e) raw[e] = raw[e] == raw[e] ? raw[e] : -INFINITY;
-      list.add(raw, t == 0);
+      for (int e = 15; e >= 0; --e)
+        if (next[e] == p.best) p.idx = best_base + ((e >> 2) * 256 + threadIdx.x) * 4 + (e & 3);
     }
   }
   if constexpr (CONF) list.finish(wtop[wave]);
@@ -419,8 +463,11 @@ __device__ __forceinline__ void merge_share(int nchunks, int L, Get get, T* out,
     const int c = ok ? q / L : 0;
     x[e] = ok ? get((size_t)c * kConfMaxK + (q - c * L)) : empty_entry<T>();
   }
+  float lm = -INFINITY;
+#pragma unroll
+  for (int e = 0; e < NV; ++e) lm = fmaxf(lm, entry_value(x[e]));
   TopList<T> list{cand, L};
-  list.add(x, true);
+  list.add(x, lm, true);
   list.finish(out);
 }
 // up to kConfSmallNV * 256 entries (a 152K vocabulary at L <= 26) take the
@@ -519,12 +566,18 @@ __global__ __launch_bounds__(256) void sample_trunc_partial_kernel(
   const float* row = logits + (size_t)i * ld;
   SamplePartial p{-INFINITY, 0.f, -INFINITY, kNoIndex, -INFINITY, 0.f};
   TopList<pair_key> list{cand[wave], L};
+  float next[16];
+  load_tile(row, chunk * tiles * kSampleChunk, vocab, next);
   for (int t = 0; t < tiles; ++t) {
     const int base = (chunk * tiles + t) * kSampleChunk;
     if (base >= vocab) break;
     float x[16];
-    load_tile(row, base, vocab, x);
-    lse16(x, p.m, p.s);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) x[e] = next[e];
+    if (t + 1 < tiles && base + kSampleChunk < vocab)
+      load_tile(row, base + kSampleChunk, vocab, next);
+    const float xmax = max16(x);
+    lse16(x, xmax, p.m, p.s);
     pair_key key[16];
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
@@ -532,7 +585,7 @@ __global__ __launch_bounds__(256) void sample_trunc_partial_kernel(
       const int v = base + ((e >> 2) * 256 + threadIdx.x) * 4 + (e & 3);
       key[e] = v < vocab && x[e] == x[e] ? make_key(x[e], v) : empty_entry<pair_key>();
     }
-    list.add(key, t == 0);
+    list.add(key, xmax, t == 0);
   }
   list.finish(wtop[wave]);
   p = block_merge<4, false>(p, red);  // its barrier also orders the four lists
@@ -628,12 +681,18 @@ __global__ __launch_bounds__(256) void sample_trunc_final_kernel(
   }
 }
 
-// 4096-entry tiles per workgroup: one while that is needed to fill the chip;
-// from kTiledGroups workgroups of four on, four, so that a wave sorts and a
-// workgroup merges its list once per 16384 entries.
+// 4096-entry tiles per workgroup.  A wave's list admits about conf_k / t of
+// tile t's entries and is sorted and merged once per chunk, so with enough
+// rows chunks are long: as many tiles as leave kTiledGroups workgroups, in equal
+// chunks (1121 scored rows x 152K logits, greedy with the confidence: 250 us
+// with four tiles, 185 with nineteen).  Below four tiles each the longer chunks
+// only idle CUs (64 rows at T = 1: 31 us with one tile, 49 with two).
 constexpr int kTiledGroups = 2048;
 static int sample_tiles(int n, int vocab) {
-  return (long long)n * ((vocab + 4 * kSampleChunk - 1) / (4 * kSampleChunk)) >= kTiledGroups ? 4 : 1;
+  const long long row = (vocab + kSampleChunk - 1) / kSampleChunk;
+  if (n * row < 4 * kTiledGroups) return 1;
+  const long long chunks = std::min<long long>(row, (kTiledGroups + n - 1) / n);
+  return (int)((row + chunks - 1) / chunks);
 }
 
 static size_t partial_bytes(int n, int nchunks) {

@@ -431,7 +431,8 @@ def test_self_confidence_ties_and_uniform(S):
     (4, 4096 + 12),      # a last tile of three lanes
     (3, 33),             # one tile, fewer lanes than entries kept
     (2, 160),            # one wave's lanes partly used, more than 64 entries
-    (260, 4 * 16384 - 4 * 4096 + 64)])  # four tiles per workgroup, the last one short
+    (700, 12 * 4096 + 64),   # five tiles per workgroup, the last ones short
+    (2100, 5 * 4096 - 4)])   # a whole row per workgroup
 @pytest.mark.parametrize("k", [1, 32])
 def test_sampler_lists_at_tile_and_list_edges(S, n, vocab, k):
     """Top-k lists where their selection changes form: rows with fewer finite
