@@ -31,8 +31,11 @@
 // Grouped form (the mixture of experts of a prefill): the m-tiles are 256-entry
 // tiles of the experts' entry lists (tile_off from the planner), a tile's
 // weights are its expert's, and its A rows are gathered per lane: the entry's
-// token row of the tiled normed input (gate/up), or the expert's SwiGLU rows
-// (down).  The gate/up epilogue writes SwiGLU rows at the entries' positions;
+// token row of the normed input (gate/up), or the expert's SwiGLU rows (down).
+// Both are row-major: a row's 32 columns of a stage are 64 consecutive bytes
+// (gathered from the tiled layout they were four 16-byte pieces of four
+// lines, and 65168 entries of the 30B-A3B shape's gate/up took 1138 us
+// instead of 596).  The gate/up epilogue writes SwiGLU rows at the entries' positions;
 // the down epilogue scatters routing weight * product into the per-slot
 // outputs [slot][token][hidden].
 #include "common.h"
@@ -109,19 +112,16 @@ __global__ __launch_bounds__(64 * kLgWaves, 1) void gemm_large_kernel(
   if constexpr (GR) {
     // one descriptor over the whole X; a row past the tile's entries gets an
     // offset past the records (the direct load then writes zeros)
-    const uint32_t recs = XT ? (uint32_t)(((M + 15) >> 4) * 16) * K * 2 : (uint32_t)M * ldx * 2;
+    static_assert(!GR || !XT, "gathered rows are row-major");
+    const uint32_t recs = (uint32_t)M * ldx * 2;
     ra[0] = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(X), 0, recs, 0x00020000);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const int j = m0 + 16 * (2 * wave + i) + (lane & 15);
       g_voff[i] = 0x80000000u;
       if (j < rows) {
-        if constexpr (XT) {
-          const int tok = g.assign[ent0 + j] / g.k;
-          g_voff[i] = (uint32_t)(((tok >> 4) * KS * 512 + (16 * (lane >> 4) + (tok & 15)) * 8) * 2);
-        } else {
-          g_voff[i] = (uint32_t)(((size_t)(ent0 + j) * ldx + 8 * (lane >> 4)) * 2);
-        }
+        const int row = EPI == 2 ? g.assign[ent0 + j] / g.k : ent0 + j;
+        g_voff[i] = (uint32_t)(((size_t)row * ldx + 8 * (lane >> 4)) * 2);
       }
     }
   }
@@ -148,9 +148,8 @@ __global__ __launch_bounds__(64 * kLgWaves, 1) void gemm_large_kernel(
   auto issue_a = [&](int st) {
     bf16_t* so = smem + (st & (kLgStages - 1)) * kLgStageElems;
     if constexpr (GR) {
-      const uint32_t dv = XT ? st * 1024u : st * 64u;
 #pragma unroll
-      for (int i = 0; i < 2; ++i) dma16(ra[0], g_voff[i] + dv, so + (2 * wave + i) * 512);
+      for (int i = 0; i < 2; ++i) dma16(ra[0], g_voff[i] + st * 64u, so + (2 * wave + i) * 512);
     } else {
       const uint32_t v = a_voff + (XT ? st * 1024u : st * 64u);
 #pragma unroll
@@ -393,7 +392,7 @@ hipError_t launch_gemm_grouped(int down, int m, int n_out, int k, const bf16_t* 
     hipLaunchKernelGGL((gemm_large_kernel<3, 0, 1>), grid, block, 0, st, x, k, m, w, n_out, k,
                        static_cast<float*>(out), n_out, nullptr, 0, max_tiles_m, tiles_n, g);
   else
-    hipLaunchKernelGGL((gemm_large_kernel<2, 1, 1>), grid, block, 0, st, x, k, m, w, n_out, k,
+    hipLaunchKernelGGL((gemm_large_kernel<2, 0, 1>), grid, block, 0, st, x, k, m, w, n_out, k,
                        nullptr, n_out, static_cast<bf16_t*>(out), 0, max_tiles_m, tiles_n, g);
   return hipGetLastError();
 }

@@ -15,12 +15,13 @@ hipError_t launch_rmsnorm(const float* x, const bf16_t* gain, int rows, int cols
                           bf16_t* out, hipStream_t st);
 // x += sum_s part[s] (split order; S == 0: nothing to add), then
 // out = bf16(RMSNorm(x) * gain) in the tiled activation layout (the GEMM
-// input).  part is [S][rows][cols] fp32.
+// input), or row-major with out_tiled 0.  part is [S][rows][cols] fp32.
 // row_idx (optional): output row r takes source row row_idx[r] of x and of
 // the partials (which then have part_rows rows); x is not written back.
 hipError_t launch_add_rmsnorm(float* x, const float* part, int S, const bf16_t* gain, int rows,
-                              int cols, float eps, bf16_t* out_tiled, hipStream_t st,
-                              const int32_t* row_idx = nullptr, int part_rows = 0);
+                              int cols, float eps, bf16_t* out, hipStream_t st,
+                              const int32_t* row_idx = nullptr, int part_rows = 0,
+                              int out_tiled = 1);
 // per packed prefill token: page-table row (its sequence) and position
 hipError_t launch_prefill_index(const int32_t* seq_starts, const int32_t* start_pos, int n_seqs,
                                 int T, int32_t* row, int32_t* pos, hipStream_t st);
@@ -94,7 +95,8 @@ constexpr int kMoeGroupRows = 256;  // rows per tile of the grouped large-M GEMM
 
 struct MoeExpertArgs {
   int n, hidden, ffn, n_experts, top_k;
-  const bf16_t* x;          // normed input, tiled [n][hidden]
+  const bf16_t* x;          // normed input [n][hidden]: tiled, or row-major (x_tiled 0)
+  int x_tiled = 1;
   const bf16_t* w_gate_up;  // [E][2 ffn][hidden], each expert packed (gate/up superblocks)
   const bf16_t* w_down;     // [E][hidden][ffn], each expert packed
   const int32_t* offsets;   // [E + 1] assignment offsets per expert
@@ -153,7 +155,7 @@ struct GroupArgs {
   const float* weights = nullptr;     // [n k] routing weights (down)
   int E = 0, k = 1, n = 0;            // experts, top-k, tokens
 };
-// down 0: gate/up of every entry, x = the tiled normed input (m = tokens),
+// down 0: gate/up of every entry, x = the row-major normed input (m = tokens),
 //   out bf16 act [n k][n_out / 2] at the entry positions (SwiGLU);
 // down 1: x = act [n k][k] row-major (m = n k entries), out fp32
 //   [k slots][n][n_out] = weight * product.  max_tiles_m >= sum of the

@@ -338,8 +338,8 @@ size_t moe_plan_scratch_bytes(int nk, int E) {
 // superblock over the whole K range, so no partial sum crosses waves (no LDS,
 // no barrier); a workgroup's four waves take 4 FPW / 4 superblocks:
 //   EPI 0 (gate/up): gate fragment f pairs with up fragment f + 2 (the 32 + 32
-//     superblock), SwiGLU in registers; X = the normed input, tiled [n][H],
-//     rows gathered by token; out act [n k][Fe] bf16, row = entry position;
+//     superblock), SwiGLU in registers; X = the normed input [n][H] (tiled, or
+//     row-major), rows gathered by token; out act [n k][Fe] bf16, row = entry position;
 //   EPI 1 (down): X = the expert's act rows; out part [k][n][H] fp32 =
 //     routing weight * product.
 // FPW is chosen so the grid fits one round of resident waves.  The expert's
@@ -389,7 +389,8 @@ __global__ __launch_bounds__(256) void moe_expert_kernel(MoeExpertArgs a) {
       const int i = min(m0 + 16 * b + r, ne - 1);
       if constexpr (EPI == 0) {
         const int t = a.assign[off + i] / a.top_k;
-        xp[b] = a.x + ((size_t)(t >> 4) * KS) * 512 + (16 * q + (t & 15)) * 8;
+        xp[b] = a.x + (a.x_tiled ? ((size_t)(t >> 4) * KS) * 512 + (16 * q + (t & 15)) * 8
+                                 : (size_t)t * a.hidden + 8 * q);
       } else {
         xp[b] = a.act + (size_t)(off + i) * a.ffn + 8 * q;
       }
@@ -412,7 +413,7 @@ __global__ __launch_bounds__(256) void moe_expert_kernel(MoeExpertArgs a) {
 #pragma unroll
       for (int b = 0; b < NB; ++b)
         f.b[b] = *reinterpret_cast<const bf16x8v*>(
-            xp[b] + (EPI == 0 ? (size_t)st * 512 : (size_t)st * 32));
+            xp[b] + (EPI == 0 && a.x_tiled ? (size_t)st * 512 : (size_t)st * 32));
     };
     auto mma = [&](const MoeFrag<NB, FPW>& f) {
 #pragma unroll

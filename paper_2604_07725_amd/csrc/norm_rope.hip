@@ -306,7 +306,8 @@ hipError_t launch_embed(const bf16_t* embed, const int32_t* tokens, int n, int h
 }
 
 // x[r] += sum_s part[s][r] in split order, written back; then the RMSNorm,
-// stored in the tiled activation layout that the projections read.
+// stored in the tiled activation layout that the projections read (or
+// row-major, for a reader that gathers rows).
 // 1024 threads per row, each owning 4 consecutive columns per 4096-column
 // pass with all split loads independent (latency, not bandwidth, is the cost).
 // With row_idx, output row r reads row row_idx[r] of x and the partials and
@@ -316,7 +317,7 @@ __global__ __launch_bounds__(1024) void add_rmsnorm_kernel(float* __restrict__ x
                                                            size_t part_stride,
                                                            const bf16_t* __restrict__ gain,
                                                            int cols, float eps,
-                                                           bf16_t* __restrict__ out,
+                                                           bf16_t* __restrict__ out, int out_tiled,
                                                            const int32_t* __restrict__ row_idx) {
   __shared__ float red[16];
   const size_t src = row_idx ? (size_t)row_idx[blockIdx.x] : (size_t)blockIdx.x;
@@ -343,7 +344,8 @@ __global__ __launch_bounds__(1024) void add_rmsnorm_kernel(float* __restrict__ x
     o.x = pack_bf16x2(v.x * inv * bf16_lo(g.x), v.y * inv * bf16_hi(g.x));
     o.y = pack_bf16x2(v.z * inv * bf16_lo(g.y), v.w * inv * bf16_hi(g.y));
     // 4 consecutive columns are contiguous in the tiled activation layout
-    *reinterpret_cast<uint2*>(out + act_tile_offset(blockIdx.x, c, cols)) = o;
+    const size_t off = out_tiled ? act_tile_offset(blockIdx.x, c, cols) : (size_t)blockIdx.x * cols + c;
+    *reinterpret_cast<uint2*>(out + off) = o;
   };
   // the first two 4-column groups of a thread (every row up to 8192 columns)
   // stay in registers across the reduction instead of being read back from x
@@ -393,6 +395,7 @@ __global__ __launch_bounds__(256) void add_rmsnorm_rows_kernel(float* __restrict
                                                                int S, const bf16_t* __restrict__ gain,
                                                                int cols, float eps,
                                                                bf16_t* __restrict__ out,
+                                                               int out_tiled,
                                                                const int32_t* __restrict__ row_idx) {
   __shared__ float red[16];
   const size_t src = row_idx ? (size_t)row_idx[blockIdx.x] : (size_t)blockIdx.x;
@@ -446,14 +449,15 @@ __global__ __launch_bounds__(256) void add_rmsnorm_rows_kernel(float* __restrict
       uint2 o;
       o.x = pack_bf16x2(v[g].x * inv * bf16_lo(gn.x), v[g].y * inv * bf16_hi(gn.x));
       o.y = pack_bf16x2(v[g].z * inv * bf16_lo(gn.y), v[g].w * inv * bf16_hi(gn.y));
-      *reinterpret_cast<uint2*>(out + act_tile_offset(blockIdx.x, c, cols)) = o;
+      const size_t off = out_tiled ? act_tile_offset(blockIdx.x, c, cols) : (size_t)blockIdx.x * cols + c;
+      *reinterpret_cast<uint2*>(out + off) = o;
     }
   }
 }
 
 hipError_t launch_add_rmsnorm(float* x, const float* part, int S, const bf16_t* gain, int rows,
-                              int cols, float eps, bf16_t* out_tiled, hipStream_t st,
-                              const int32_t* row_idx, int part_rows) {
+                              int cols, float eps, bf16_t* out, hipStream_t st,
+                              const int32_t* row_idx, int part_rows, int out_tiled) {
   if (rows == 0) return hipSuccess;
   if (S > 16) return hipErrorInvalidValue;
   const size_t stride = (size_t)(row_idx ? part_rows : rows) * cols;
@@ -462,7 +466,7 @@ hipError_t launch_add_rmsnorm(float* x, const float* part, int S, const bf16_t* 
     const int ng = (cols + 1023) / 1024;
     auto go = [&](auto kern) {
       hipLaunchKernelGGL(kern, dim3(rows), dim3(256), 0, st, x, part, s_eff, gain, cols, eps,
-                         out_tiled, row_idx);
+                         out, out_tiled, row_idx);
     };
     if (ng <= 2) go(add_rmsnorm_rows_kernel<2>);
     else if (ng <= 4) go(add_rmsnorm_rows_kernel<4>);
@@ -470,7 +474,7 @@ hipError_t launch_add_rmsnorm(float* x, const float* part, int S, const bf16_t* 
     return hipGetLastError();
   }
   hipLaunchKernelGGL(add_rmsnorm_kernel, dim3(rows), dim3(1024), 0, st, x, part, s_eff, stride,
-                     gain, cols, eps, out_tiled, row_idx);
+                     gain, cols, eps, out, out_tiled, row_idx);
   return hipGetLastError();
 }
 

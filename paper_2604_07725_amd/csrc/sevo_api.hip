@@ -1114,14 +1114,15 @@ PrefillLayout prefill_layout(const sevo_model_config& c, int T, int R, int moe_c
 }
 
 // One projection of a prefill: the large-M kernel when it applies, else the
-// decode kernel in one K split (no workspace).  X in the tiled layout.
+// decode kernel in one K split (no workspace).  X tiled, or row-major.
 hipError_t prefill_gemm(int m, int n_out, int k, int mode, const sevo::bf16_t* x,
-                        const void* w, void* out, int out_tiled, hipStream_t st) {
+                        const void* w, void* out, int out_tiled, hipStream_t st,
+                        int x_tiled = 1) {
   const sevo::bf16_t* wb = static_cast<const sevo::bf16_t*>(w);
   if (m >= sevo::kLargeGemmMinM && sevo::gemm_large_supported(m, n_out, k))
-    return sevo::launch_gemm_large(m, n_out, k, k, 1, mode, x, wb, out, out_tiled, st);
+    return sevo::launch_gemm_large(m, n_out, k, k, x_tiled, mode, x, wb, out, out_tiled, st);
   const sevo::LinearPlan p = sevo::plan_linear(m, n_out, k, 1, mode);
-  return sevo::launch_linear(m, n_out, k, k, 1, mode, p, x, wb, out, out_tiled, nullptr, st);
+  return sevo::launch_linear(m, n_out, k, k, x_tiled, mode, p, x, wb, out, out_tiled, nullptr, st);
 }
 
 // Entries per expert (n k / E on average) from which a prefill chunk's experts
@@ -1129,15 +1130,15 @@ hipError_t prefill_gemm(int m, int n_out, int k, int mode, const sevo::bf16_t* x
 // once per tile) instead of the decode kernels (16-64-row tiles).
 constexpr int kPrefillGroupedMinPerExpert = 32;
 
-// The MoE FFN of prefill rows c0 .. c0 + nc (c0 a multiple of 16) on the tiled
-// normed input h: router GEMM, top-k, entry lists, expert gate/up + down into
+// The MoE FFN of prefill rows c0 .. c0 + nc (c0 a multiple of 16) on the
+// row-major normed input h (the experts gather its rows): router GEMM, top-k, entry lists, expert gate/up + down into
 // per-slot outputs, then part[c0 + i] = their slot-order sum.
 hipError_t run_moe_prefill_chunk(const sevo_model* m, int l, int c0, int nc,
                                  const sevo::bf16_t* h, char* ws, const PrefillLayout& L,
                                  float* part, hipStream_t st) {
   const sevo_model_config& c = m->cfg;
   const int H = c.hidden, E = c.n_experts, k = c.n_experts_active;
-  const sevo::bf16_t* hc = h + (size_t)(c0 / 16) * (H / 32) * 512;  // 16-row blocks
+  const sevo::bf16_t* hc = h + (size_t)c0 * H;
   float* rl = reinterpret_cast<float*>(ws + L.m_router);
   int32_t* sel = reinterpret_cast<int32_t*>(ws + L.m_sel);
   float* wts = reinterpret_cast<float*>(ws + L.m_w);
@@ -1149,7 +1150,7 @@ hipError_t run_moe_prefill_chunk(const sevo_model* m, int l, int c0, int nc,
   hipError_t e;
   {
     ProfScope ps(SEVO_PROF_MOE_ROUTE, st);
-    e = prefill_gemm(nc, E, H, SEVO_LINEAR_STORE, hc, m->w_router[l], rl, 0, st);
+    e = prefill_gemm(nc, E, H, SEVO_LINEAR_STORE, hc, m->w_router[l], rl, 0, st, 0);
     if (e == hipSuccess) e = sevo::launch_moe_route(rl, 1, nc, E, k, sel, wts, st);
     if (e == hipSuccess)
       e = sevo::launch_moe_plan(sel, nc * k, E, off, asg, st, grouped ? tiles : nullptr,
@@ -1176,6 +1177,7 @@ hipError_t run_moe_prefill_chunk(const sevo_model* m, int l, int c0, int nc,
   }
   sevo::MoeExpertArgs ma;
   ma.n = nc; ma.hidden = H; ma.ffn = c.expert_ffn; ma.n_experts = E; ma.top_k = k; ma.x = hc;
+  ma.x_tiled = 0;
   ma.w_gate_up = static_cast<const sevo::bf16_t*>(m->w_expert_gate_up[l]);
   ma.w_down = static_cast<const sevo::bf16_t*>(m->w_expert_down[l]);
   ma.offsets = off;
@@ -1307,7 +1309,7 @@ SEVO_API sevo_status sevo_prefill_confidence(sevo_model* m, const sevo_prefill_a
     if (e == hipSuccess) {
       ProfScope ps(SEVO_PROF_NORM, st);
       e = sevo::launch_add_rmsnorm(x, nullptr, 0, static_cast<const sevo::bf16_t*>(m->ffn_norm[l]),
-                                   T, H, c.rms_eps, h, st);
+                                   T, H, c.rms_eps, h, st, nullptr, 0, moe ? 0 : 1);
     }
     if (moe) {
       // the mixture of experts, a chunk of tokens at a time: per-slot outputs
