@@ -494,7 +494,8 @@ sevo_status sevo_add_rmsnorm(float* x, const float* partials, int32_t n_partials
  *                                else row-major with row stride ldx, ldx % 8 == 0)
  *        SEVO_LINEAR_OUT_TILED   SWIGLU output in the tiled activation layout
  * k % 32 == 0; n_out % 64 == 0.  k_splits 0 = chosen by the library (SWIGLU
- * always uses one split). */
+ * always uses one split; from m = 256 on the library always chooses, and a
+ * workspace below sevo_linear_workspace_bytes, or none, means one split). */
 #define SEVO_LINEAR_STORE 0
 #define SEVO_LINEAR_ADD 1
 #define SEVO_LINEAR_SWIGLU 2
@@ -511,11 +512,11 @@ typedef struct {
 
 sevo_status sevo_linear(const sevo_linear_args* a, void* stream);
 size_t sevo_linear_workspace_bytes(int32_t m, int32_t n_out, int32_t k, int32_t k_splits);
-/* The plan of the skinny kernel that sevo_linear runs for m < 256 (and the
- * decode step for its projections): plan[0] = K splits, plan[1] = k per split,
- * plan[2] = 16-row weight blocks per workgroup (for SWIGLU gate and up blocks,
- * an even count).  The planner aims at one round of 256 equal workgroups (one
- * per CU).  Writes plan[0..2] (caller-owned host memory) and returns SEVO_OK;
+/* The plan that sevo_linear runs for m < 256 (and the decode step for its
+ * projections), of the skinny kernel up to 128 rows and of the tiled one
+ * above: plan[0] = K splits, plan[1] = k per split, plan[2] = 16-row weight
+ * blocks per workgroup (for SWIGLU gate and up blocks, an even count).  The
+ * planner aims at one round of 256 equal workgroups (one per CU).  Writes plan[0..2] (caller-owned host memory) and returns SEVO_OK;
  * INVALID_ARGUMENT for a null plan or a shape outside m in [1, 255],
  * n_out % 64 == 0, k % 32 == 0, mode in {STORE, ADD, SWIGLU}. */
 sevo_status sevo_linear_plan(int32_t m, int32_t n_out, int32_t k, int32_t k_splits, int32_t mode,

@@ -127,9 +127,16 @@ struct LinearPlan {
   int k_splits;
   int k_chunk;
   int rb = 4;  // 16-row weight blocks per workgroup (SwiGLU: gate + up blocks)
+  int mb = 1;  // 16-row activation blocks per workgroup
+  int tile = 0;  // 0: the skinny kernel; else a tile shape of gemm_large.hip
 };
-LinearPlan plan_linear(int m, int n_out, int k, int k_splits, int mode);
-size_t linear_workspace_bytes(int m, int n_out, int k, int k_splits, int mode);
+// max_mb 4: the skinny kernel in M tiles of at most 64 rows (the other plans
+// above 64 rows may split K further, and need a larger workspace).
+// max_splits bounds a split count that the library chooses
+constexpr int kLinearMaxMb = 8, kLinearSmallMb = 4;
+LinearPlan plan_linear(int m, int n_out, int k, int k_splits, int mode,
+                       int max_mb = kLinearMaxMb, int max_splits = 16);
+size_t linear_workspace_bytes(int m, int n_out, const LinearPlan& p);
 // X operand: row-major with row stride ldx (x_tiled == 0) or the tiled
 // activation layout; W: the packed weight layout (gate/up interleaved for SWIGLU).
 // complete Y = X W^T with the STORE / ADD / SWIGLU epilogue (SWIGLU output
@@ -142,10 +149,13 @@ hipError_t launch_linear(int m, int n_out, int k, int ldx, int x_tiled, int mode
 hipError_t launch_linear_partials(int m, int n_out, int k, int ldx, int x_tiled,
                                   const LinearPlan& plan, const bf16_t* x, const bf16_t* w,
                                   float* out, int accumulate, hipStream_t st);
-// ---- gemm_large.hip: one-pass Y = X W^T for large M (prefill token counts),
-// same operand layouts and epilogue modes as launch_linear (no workspace)
+// ---- gemm_large.hip: Y = X W^T in LDS tiles for more than 64 rows, same
+// operand layouts and epilogue modes as launch_linear; with K split, mode 0
+// writes the partials [split][m][n].  fixed_splits 0: chosen, at most max_splits
+constexpr int kTileMinM = 65;
+// from here on a caller's k_splits is not taken and no workspace is required
 constexpr int kLargeGemmMinM = 256;
-bool gemm_large_supported(int m, int n_out, int k);
+LinearPlan plan_tiles(int m, int n_out, int k, int mode, int fixed_splits, int max_splits);
 // grouped form (mixture of experts): m-tiles are 256-entry tiles of the
 // experts' entry lists; the expert's weights at w + e n_out k
 struct GroupArgs {
@@ -164,8 +174,8 @@ hipError_t launch_gemm_grouped(int down, int m, int n_out, int k, const bf16_t* 
                                const bf16_t* w, void* out, const GroupArgs& g, int max_tiles_m,
                                hipStream_t st);
 hipError_t launch_gemm_large(int m, int n_out, int k, int ldx, int x_tiled, int mode,
-                             const bf16_t* x, const bf16_t* w, void* out, int out_tiled,
-                             hipStream_t st);
+                             const LinearPlan& plan, const bf16_t* x, const bf16_t* w, void* out,
+                             int out_tiled, hipStream_t st);
 // row-major [n_out][k] -> packed weight layout; gate_up: rows 0..n_out/2-1 are
 // gate rows and the rest up rows, interleaved per superblock (32 + 32)
 hipError_t launch_pack_weight(const bf16_t* src, bf16_t* dst, int n_out, int k, int gate_up,

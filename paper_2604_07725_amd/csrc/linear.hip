@@ -1,14 +1,14 @@
 // Skinny bf16 GEMM Y = X W^T on the gfx950 matrix cores, for the QKV, output,
 // gate/up and down projections and the LM head of a decode step.
 //
-// At decode the batch M is the population size (<= 64 per tile), so the
+// At decode the batch M is the population size (<= 128 per tile), so the
 // arithmetic intensity is M flop per weight byte: far below the MFMA ridge,
 // the kernel is a weight stream and is designed for HBM bandwidth.
 //   * operands are stored fragment-major (common.h): every load of an MFMA
 //     16x16x32 operand fragment is one contiguous 1 KB read (half-line reads
 //     of row-major rows measured about a third slower);
 //   * one 256-thread workgroup per (RB row blocks of 16 weight rows, K split,
-//     M tile of up to 64 rows).  The planner picks RB and the split count so
+//     M tile of up to 64 rows; 128 for the narrower gate/up matrices).  The planner picks RB and the split count so
 //     that a projection is about one round of 256 equal workgroups, one per
 //     CU (a 384-workgroup gate/up or a 192-workgroup QKV left CUs with half
 //     or double the bytes of the others); more row blocks per workgroup also
@@ -57,7 +57,8 @@ __global__ __launch_bounds__(256, (linear_min_blocks<MB, RB>())) void linear_ker
     int k_chunk, float* __restrict__ out, int accumulate, bf16_t* __restrict__ out_bf16,
     int out_tiled) {
   static_assert(EPI != 2 || RB % 2 == 0, "SwiGLU row blocks come in gate/up pairs");
-  __shared__ f32x4 red[4][RB][MB][64];
+  constexpr int MR = MB < 4 ? MB : 4;  // activation blocks per reduction pass
+  __shared__ f32x4 red[4][RB][MR][64];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int s = blockIdx.y;
@@ -160,46 +161,52 @@ __global__ __launch_bounds__(256, (linear_min_blocks<MB, RB>())) void linear_ker
     }
   }
 
+  // the waves' tiles are summed through LDS, four activation blocks at a time
+  // (an eight-block tile in two passes: its four copies would not fit)
 #pragma unroll
-  for (int i = 0; i < RB; ++i)
+  for (int b0 = 0; b0 < MB; b0 += MR) {
+    if (b0 > 0) __syncthreads();
 #pragma unroll
-    for (int b = 0; b < MB; ++b) red[wave][i][b][lane] = acc[i][b];
-  __syncthreads();
-  // D[i][j] of tile (row block, b): lane holds j = lane % 16 (activation row)
-  // and i = 4 (lane / 16) + 0..3 (weight row) -> 4 consecutive output columns.
-  if constexpr (EPI == 2) {
-    const int F = N / 2;
-    for (int idx = threadIdx.x; idx < (RB / 2) * MB * 64; idx += 256) {
-      const int l = idx & 63;
-      const int tb = idx >> 6;
-      const int pi = tb / MB, b = tb - pi * MB;
-      const int p = blockIdx.x * (RB / 2) + pi;
-      const int gi = 2 * pi, ui = 2 * pi + 1;
-      const f32x4 g = red[0][gi][b][l] + red[1][gi][b][l] + red[2][gi][b][l] + red[3][gi][b][l];
-      const f32x4 u = red[0][ui][b][l] + red[1][ui][b][l] + red[2][ui][b][l] + red[3][ui][b][l];
-      const int m = m0 + 16 * b + (l & 15);
-      const int j = (p >> 1) * 32 + 16 * (p & 1) + 4 * (l >> 4);
-      if (m < M && 2 * p < nrb) {
-        uint2 o;
-        o.x = pack_bf16x2(g.x / (1.f + __expf(-g.x)) * u.x, g.y / (1.f + __expf(-g.y)) * u.y);
-        o.y = pack_bf16x2(g.z / (1.f + __expf(-g.z)) * u.z, g.w / (1.f + __expf(-g.w)) * u.w);
-        const size_t off = out_tiled ? act_tile_offset(m, j, F) : (size_t)m * F + j;
-        *reinterpret_cast<uint2*>(out_bf16 + off) = o;
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+      for (int b = 0; b < MR; ++b) red[wave][i][b][lane] = acc[i][b0 + b];
+    __syncthreads();
+    // D[i][j] of tile (row block, b): lane holds j = lane % 16 (activation row)
+    // and i = 4 (lane / 16) + 0..3 (weight row) -> 4 consecutive output columns.
+    if constexpr (EPI == 2) {
+      const int F = N / 2;
+      for (int idx = threadIdx.x; idx < (RB / 2) * MR * 64; idx += 256) {
+        const int l = idx & 63;
+        const int tb = idx >> 6;
+        const int pi = tb / MR, b = tb - pi * MR;
+        const int p = blockIdx.x * (RB / 2) + pi;
+        const int gi = 2 * pi, ui = 2 * pi + 1;
+        const f32x4 g = red[0][gi][b][l] + red[1][gi][b][l] + red[2][gi][b][l] + red[3][gi][b][l];
+        const f32x4 u = red[0][ui][b][l] + red[1][ui][b][l] + red[2][ui][b][l] + red[3][ui][b][l];
+        const int m = m0 + 16 * (b0 + b) + (l & 15);
+        const int j = (p >> 1) * 32 + 16 * (p & 1) + 4 * (l >> 4);
+        if (m < M && 2 * p < nrb) {
+          uint2 o;
+          o.x = pack_bf16x2(g.x / (1.f + __expf(-g.x)) * u.x, g.y / (1.f + __expf(-g.y)) * u.y);
+          o.y = pack_bf16x2(g.z / (1.f + __expf(-g.z)) * u.z, g.w / (1.f + __expf(-g.w)) * u.w);
+          const size_t off = out_tiled ? act_tile_offset(m, j, F) : (size_t)m * F + j;
+          *reinterpret_cast<uint2*>(out_bf16 + off) = o;
+        }
       }
-    }
-  } else {
-    for (int idx = threadIdx.x; idx < RB * MB * 64; idx += 256) {
-      const int l = idx & 63;
-      const int tb = idx >> 6;
-      const int i = tb / MB, b = tb - i * MB;
-      const f32x4 v = red[0][i][b][l] + red[1][i][b][l] + red[2][i][b][l] + red[3][i][b][l];
-      const int m = m0 + 16 * b + (l & 15);
-      const int rbk = blockIdx.x * RB + i;
-      const int n = rbk * 16 + 4 * (l >> 4);
-      if (m < M && rbk < nrb) {
-        f32x4* dst = reinterpret_cast<f32x4*>(out + (size_t)s * M * N + (size_t)m * N + n);
-        if (accumulate) *dst = *dst + v;
-        else *dst = v;
+    } else {
+      for (int idx = threadIdx.x; idx < RB * MR * 64; idx += 256) {
+        const int l = idx & 63;
+        const int tb = idx >> 6;
+        const int i = tb / MR, b = tb - i * MR;
+        const f32x4 v = red[0][i][b][l] + red[1][i][b][l] + red[2][i][b][l] + red[3][i][b][l];
+        const int m = m0 + 16 * (b0 + b) + (l & 15);
+        const int rbk = blockIdx.x * RB + i;
+        const int n = rbk * 16 + 4 * (l >> 4);
+        if (m < M && rbk < nrb) {
+          f32x4* dst = reinterpret_cast<f32x4*>(out + (size_t)s * M * N + (size_t)m * N + n);
+          if (accumulate) *dst = *dst + v;
+          else *dst = v;
+        }
       }
     }
   }
@@ -254,20 +261,40 @@ __global__ __launch_bounds__(256) void pack_weight_kernel(const bf16_t* __restri
   }
 }
 
-static int pick_mb(int m) { return m > 32 ? 4 : (m > 16 ? 2 : 1); }
+// 16-row activation blocks per workgroup: the fewest of 1, 2, 4 that hold m
+// rows, and above 64 rows (a gate/up matrix, see plan_linear) 4 or 8.  A
+// second M tile of 64 streams the weights again, so a large matrix takes one
+// tile of eight blocks (one wave per SIMD): 201 MB at m = 128 65.7 -> 43.3 us.
+// Small ones come from the Infinity Cache the second time and keep 64 rows.
+constexpr double kEightBlockBytes = 64e6;
+static int pick_mb(int m, int n_out, int k, int max_mb) {
+  if (m > 64) return max_mb > 4 && 2.0 * n_out * k >= kEightBlockBytes ? 8 : 4;
+  return m > 32 ? 4 : m > 16 ? 2 : 1;
+}
 
 // Row blocks per workgroup with an instantiated kernel: at least 3 for a
 // 64-row M tile (fewer re-read each activation fragment for too few weight
 // fragments), at most what the registers hold; SwiGLU takes whole pairs.
-static int rb_min(int mb) { return mb == 4 ? 3 : 2; }
-static int rb_max(int mb) { return mb == 4 ? 8 : (mb == 2 ? 12 : 16); }
+constexpr int rb_min(int mb) { return mb >= 4 ? 3 : 2; }
+constexpr int rb_max(int mb) { return mb == 8 ? 6 : (mb == 4 ? 8 : (mb == 2 ? 12 : 16)); }
 static const int kRbSet[] = {2, 3, 4, 5, 6, 8, 10, 12, 14, 16};
-static bool rb_ok(int rb, int mb, int swiglu) {
+constexpr bool rb_ok(int rb, int mb, int swiglu) {
   return rb >= rb_min(mb) && rb <= rb_max(mb) && (!swiglu || rb % 2 == 0);
 }
 
-LinearPlan plan_linear(int m, int n_out, int k, int k_splits, int mode) {
-  const int mb = pick_mb(m);
+LinearPlan plan_linear(int m, int n_out, int k, int k_splits, int mode, int max_mb,
+                       int max_splits) {
+  // more than 64 rows: LDS tiles, which read the weights once per 128-256 rows
+  // (us, against this kernel's tiles of 128 rows: LM head 151936 x 4096 at m =
+  // 65 / 128 336 / 361 -> 248 / 271, down 4096 x 12288 28 / 32 -> 22 / 25 and 5,
+  // 32B-class gate/up 129 / 148 -> 93 / 99; at m = 160 8B-class gate/up 78 -> 60,
+  // QKV 26 -> 22, output 21 -> 16).  A gate/up matrix cannot split K: up to 128
+  // rows, one too narrow for 192 tiles of 256 columns stays here (24576 x 4096
+  // at m = 128: 43 us, tiles 49)
+  if (m >= kTileMinM && max_mb > kLinearSmallMb &&
+      !(mode == 2 && m <= 128 && n_out < 192 * 256))
+    return plan_tiles(m, n_out, k, mode, m < kLargeGemmMinM ? k_splits : 0, max_splits);
+  const int mb = pick_mb(m, n_out, k, max_mb);
   const int mt = (m + 16 * mb - 1) / (16 * mb);
   const int swiglu = mode == 2;
   const int per_unit = swiglu ? 2 : 1;  // row blocks per unit (a gate/up pair)
@@ -303,6 +330,7 @@ LinearPlan plan_linear(int m, int n_out, int k, int k_splits, int mode) {
     return best;
   };
   LinearPlan p;
+  p.mb = mb;
   // split counts: SwiGLU needs the whole K range; otherwise the caller's, or
   // the smallest of 1, 2, 4, ... (at least 1024 k per split, so each wave
   // streams 8 steps or more) whose plan fills 95% of its last round or needs
@@ -318,7 +346,7 @@ LinearPlan plan_linear(int m, int n_out, int k, int k_splits, int mode) {
   else if (k_splits > 0) cands[nc++] = k_splits;
   else
     for (int s = 1; s <= 16; s *= 2)
-      if (s == 1 || chunk_of(s) >= min_chunk) cands[nc++] = s;
+      if (s == 1 || (s <= max_splits && chunk_of(s) >= min_chunk)) cands[nc++] = s;
   double best_eff = -1.0;
   for (int i = 0; i < nc; ++i) {
     const int chunk = chunk_of(cands[i]);
@@ -337,8 +365,7 @@ LinearPlan plan_linear(int m, int n_out, int k, int k_splits, int mode) {
   return p;
 }
 
-size_t linear_workspace_bytes(int m, int n_out, int k, int k_splits, int mode) {
-  const LinearPlan p = plan_linear(m, n_out, k, k_splits, mode);
+size_t linear_workspace_bytes(int m, int n_out, const LinearPlan& p) {
   if (p.k_splits == 1) return 0;
   return (size_t)p.k_splits * m * n_out * sizeof(float);
 }
@@ -358,9 +385,7 @@ struct LinearLaunch {
 
 template <int MB, int RB, int EPI, int XT>
 static bool launch_one(const LinearLaunch& a) {
-  constexpr bool inst = RB >= (MB == 4 ? 3 : 2) && RB <= (MB == 4 ? 8 : (MB == 2 ? 12 : 16)) &&
-                        (EPI != 2 || RB % 2 == 0);
-  if constexpr (inst) {
+  if constexpr (rb_ok(RB, MB, EPI == 2)) {
     hipLaunchKernelGGL((linear_kernel<MB, RB, EPI, XT>), a.grid, dim3(256), 0, a.st, a.x, a.ldx,
                        a.m, a.w, a.n_out, a.k, a.k_chunk, a.dst, a.acc, a.out_bf16, a.out_tiled);
     return true;
@@ -389,14 +414,15 @@ static bool launch_rb(int rb, const LinearLaunch& a) {
 template <int EPI, int XT>
 static hipError_t launch_linear_kernel(int mb, int rb, const LinearLaunch& a) {
   bool ok;
-  if (mb == 4) ok = launch_rb<4, EPI, XT>(rb, a);
+  if (mb == 8) ok = launch_rb<8, EPI, XT>(rb, a);
+  else if (mb == 4) ok = launch_rb<4, EPI, XT>(rb, a);
   else if (mb == 2) ok = launch_rb<2, EPI, XT>(rb, a);
   else ok = launch_rb<1, EPI, XT>(rb, a);
   return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
 
 static dim3 linear_grid(int m, int n_out, int mode, const LinearPlan& plan) {
-  const int mb = pick_mb(m);
+  const int mb = plan.mb;
   const int per_unit = mode == 2 ? 2 : 1;
   const int units = (n_out / 16) / per_unit;
   const int upw = plan.rb / per_unit;
@@ -408,21 +434,25 @@ hipError_t launch_linear_partials(int m, int n_out, int k, int ldx, int x_tiled,
                                   const LinearPlan& plan, const bf16_t* x, const bf16_t* w,
                                   float* out, int accumulate, hipStream_t st) {
   if (m == 0) return hipSuccess;
+  if (plan.tile)
+    return launch_gemm_large(m, n_out, k, ldx, x_tiled, accumulate ? 1 : 0, plan, x, w, out, 0, st);
   const LinearLaunch a{linear_grid(m, n_out, 0, plan), st, x, ldx, m, w, n_out, k, plan.k_chunk,
                        out, accumulate, nullptr, 0};
-  return x_tiled ? launch_linear_kernel<0, 1>(pick_mb(m), plan.rb, a)
-                 : launch_linear_kernel<0, 0>(pick_mb(m), plan.rb, a);
+  return x_tiled ? launch_linear_kernel<0, 1>(plan.mb, plan.rb, a)
+                 : launch_linear_kernel<0, 0>(plan.mb, plan.rb, a);
 }
 
 hipError_t launch_linear(int m, int n_out, int k, int ldx, int x_tiled, int mode,
                          const LinearPlan& plan, const bf16_t* x, const bf16_t* w, void* out,
                          int out_tiled, float* workspace, hipStream_t st) {
   if (m == 0) return hipSuccess;
+  if (mode == 2 && plan.tile)
+    return launch_gemm_large(m, n_out, k, ldx, x_tiled, 2, plan, x, w, out, out_tiled, st);
   if (mode == 2) {
     const LinearLaunch a{linear_grid(m, n_out, 2, plan), st, x, ldx, m, w, n_out, k,
                          plan.k_chunk, nullptr, 0, reinterpret_cast<bf16_t*>(out), out_tiled};
-    return x_tiled ? launch_linear_kernel<2, 1>(pick_mb(m), plan.rb, a)
-                   : launch_linear_kernel<2, 0>(pick_mb(m), plan.rb, a);
+    return x_tiled ? launch_linear_kernel<2, 1>(plan.mb, plan.rb, a)
+                   : launch_linear_kernel<2, 0>(plan.mb, plan.rb, a);
   }
   if (plan.k_splits == 1)
     return launch_linear_partials(m, n_out, k, ldx, x_tiled, plan, x, w,

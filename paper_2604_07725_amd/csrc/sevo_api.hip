@@ -604,7 +604,9 @@ SEVO_API size_t sevo_linear_workspace_bytes(int32_t m, int32_t n_out, int32_t k,
                                             int32_t k_splits) {
   if (m <= 0 || n_out <= 0 || k <= 0) return 0;
   // the STORE / ADD plan; SwiGLU needs no workspace
-  return round_up(sevo::linear_workspace_bytes(m, n_out, k, k_splits, SEVO_LINEAR_STORE), 256);
+  return round_up(sevo::linear_workspace_bytes(
+                      m, n_out, sevo::plan_linear(m, n_out, k, k_splits, SEVO_LINEAR_STORE)),
+                  256);
 }
 
 SEVO_API sevo_status sevo_linear_plan(int32_t m, int32_t n_out, int32_t k, int32_t k_splits,
@@ -628,15 +630,17 @@ SEVO_API sevo_status sevo_linear(const sevo_linear_args* a, void* stream) {
   if (a->m == 0) return SEVO_OK;
   if (!a->x || !a->w || !a->out || !aligned16(a->x) || !aligned16(a->w) || !aligned16(a->out))
     return fail(SEVO_ERR_INVALID_ARGUMENT, "null or misaligned pointer");
-  if (a->m >= sevo::kLargeGemmMinM && sevo::gemm_large_supported(a->m, a->n_out, a->k)) {
-    hipError_t e = sevo::launch_gemm_large(
-        a->m, a->n_out, a->k, a->ldx, (a->flags & SEVO_LINEAR_X_TILED) ? 1 : 0, a->mode,
-        static_cast<const sevo::bf16_t*>(a->x), static_cast<const sevo::bf16_t*>(a->w), a->out,
-        (a->flags & SEVO_LINEAR_OUT_TILED) ? 1 : 0, static_cast<hipStream_t>(stream));
-    return e == hipSuccess ? SEVO_OK : hip_fail(e, "sevo_linear (large m)");
+  sevo::LinearPlan plan = sevo::plan_linear(a->m, a->n_out, a->k, a->k_splits, a->mode);
+  size_t need = sevo::linear_workspace_bytes(a->m, a->n_out, plan);
+  if (need > 0 && (!a->workspace || a->workspace_bytes < need)) {
+    // a workspace sized for M tiles of 64 rows keeps them; from 256 rows on
+    // none is required
+    plan = a->m >= sevo::kLargeGemmMinM
+               ? sevo::plan_linear(a->m, a->n_out, a->k, 0, a->mode, sevo::kLinearMaxMb, 1)
+               : sevo::plan_linear(a->m, a->n_out, a->k, a->k_splits, a->mode,
+                                   sevo::kLinearSmallMb);
+    need = sevo::linear_workspace_bytes(a->m, a->n_out, plan);
   }
-  const sevo::LinearPlan plan = sevo::plan_linear(a->m, a->n_out, a->k, a->k_splits, a->mode);
-  const size_t need = sevo::linear_workspace_bytes(a->m, a->n_out, a->k, a->k_splits, a->mode);
   if (need > 0) {
     if (!a->workspace || !aligned16(a->workspace) || a->workspace_bytes < need)
       return fail(SEVO_ERR_WORKSPACE_TOO_SMALL, "linear needs %zu workspace bytes, got %zu", need,
@@ -743,23 +747,24 @@ struct StepLayout {
   sevo::LinearPlan p_qkv, p_o, p_gu, p_d, p_lm, p_router;
 };
 
-StepLayout step_layout(const sevo_model_config& c, int n, int max_pages, int num_splits) {
+StepLayout step_layout(const sevo_model_config& c, int n, int max_pages, int num_splits,
+                       int max_mb = sevo::kLinearMaxMb) {
   StepLayout L;
   const int qd = c.n_q_heads * c.head_dim;
   const int qkvd = (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim;
   resolve_splits(n, c.n_kv_heads, max_pages, num_splits, &L.S, &L.chunk);
-  L.p_qkv = sevo::plan_linear(n, qkvd, c.hidden, 0, SEVO_LINEAR_STORE);
-  L.p_o = sevo::plan_linear(n, c.hidden, qd, 0, SEVO_LINEAR_STORE);
+  L.p_qkv = sevo::plan_linear(n, qkvd, c.hidden, 0, SEVO_LINEAR_STORE, max_mb);
+  L.p_o = sevo::plan_linear(n, c.hidden, qd, 0, SEVO_LINEAR_STORE, max_mb);
   const bool moe = c.n_experts > 0;
   const int kact = moe ? c.n_experts_active : 0;
   if (!moe) {
-    L.p_gu = sevo::plan_linear(n, 2 * c.ffn, c.hidden, 0, SEVO_LINEAR_SWIGLU);
-    L.p_d = sevo::plan_linear(n, c.hidden, c.ffn, 0, SEVO_LINEAR_STORE);
+    L.p_gu = sevo::plan_linear(n, 2 * c.ffn, c.hidden, 0, SEVO_LINEAR_SWIGLU, max_mb);
+    L.p_d = sevo::plan_linear(n, c.hidden, c.ffn, 0, SEVO_LINEAR_STORE, max_mb);
   } else {
     L.p_gu = L.p_d = sevo::LinearPlan{1, c.hidden};
-    L.p_router = sevo::plan_linear(n, c.n_experts, c.hidden, 0, SEVO_LINEAR_STORE);
+    L.p_router = sevo::plan_linear(n, c.n_experts, c.hidden, 0, SEVO_LINEAR_STORE, max_mb);
   }
-  L.p_lm = sevo::plan_linear(n, c.vocab, c.hidden, 1, SEVO_LINEAR_STORE);
+  L.p_lm = sevo::plan_linear(n, c.vocab, c.hidden, 1, SEVO_LINEAR_STORE, max_mb);
   size_t off = 0;
   auto take = [&](size_t bytes) {
     const size_t o = off;
@@ -790,6 +795,14 @@ StepLayout step_layout(const sevo_model_config& c, int n, int max_pages, int num
   }
   L.total = off;
   return L;
+}
+
+// The layout of a step in ws_bytes: a workspace sized for the skinny kernel's M
+// tiles of 64 rows, but too small for the other plans, keeps the former.
+StepLayout fitting_step_layout(const sevo_model_config& c, int n, int max_pages, int num_splits,
+                               size_t ws_bytes) {
+  const StepLayout L = step_layout(c, n, max_pages, num_splits);
+  return ws_bytes >= L.total ? L : step_layout(c, n, max_pages, num_splits, sevo::kLinearSmallMb);
 }
 
 // The MoE FFN of layer l on the tiled normed input h: router GEMM, top-k,
@@ -859,7 +872,7 @@ SEVO_API sevo_status sevo_decode_step(sevo_model* m, const sevo_step_args* a, vo
     if (!a->kv_pools[l] || !aligned16(a->kv_pools[l]))
       return fail(SEVO_ERR_INVALID_ARGUMENT, "layer %d: null or misaligned KV pool", l);
   const int n = a->n;
-  const StepLayout L = step_layout(c, n, a->max_pages, a->num_splits);
+  const StepLayout L = fitting_step_layout(c, n, a->max_pages, a->num_splits, a->workspace_bytes);
   if (a->workspace_bytes < L.total)
     return fail(SEVO_ERR_WORKSPACE_TOO_SMALL, "decode step needs %zu workspace bytes, got %zu",
                 L.total, a->workspace_bytes);
@@ -1029,7 +1042,7 @@ SEVO_API sevo_status sevo_moe_ffn(const sevo_model* m, int32_t layer, const void
   if (!h || !out_experts || !out_weights || !out_partials || !workspace || !aligned16(h) ||
       !aligned16(out_partials) || !aligned16(workspace))
     return fail(SEVO_ERR_INVALID_ARGUMENT, "null or misaligned pointer");
-  const StepLayout L = step_layout(c, n, 1, 1);
+  const StepLayout L = fitting_step_layout(c, n, 1, 1, workspace_bytes);
   if (workspace_bytes < L.total)
     return fail(SEVO_ERR_WORKSPACE_TOO_SMALL, "MoE FFN needs %zu workspace bytes, got %zu",
                 L.total, workspace_bytes);
@@ -1048,6 +1061,8 @@ constexpr int kPrefillMoeRows = 65536;  // tokens per MoE FFN chunk (a multiple 
 
 struct PrefillLayout {
   size_t row, pos, x, h, qkv, q, o, a, part, hf, logits, sample, conf, ids, lps, total;
+  sevo::LinearPlan p_qkv, p_o, p_gu, p_d;
+  size_t router_rows;  // rows of router logits (over all splits) that fit
   // MoE FFN, one token chunk at a time: router logits, routing, entry lists,
   // SwiGLU rows, per-slot outputs
   size_t m_router, m_sel, m_w, m_off, m_assign, m_act, m_slots, m_tiles, m_plan;
@@ -1055,8 +1070,21 @@ struct PrefillLayout {
   int mc;  // tokens per MoE chunk
 };
 
-PrefillLayout prefill_layout(const sevo_model_config& c, int T, int R, int moe_chunk = 0) {
+// split false: no K splits (the sizes of a workspace without their partials)
+PrefillLayout prefill_layout(const sevo_model_config& c, int T, int R, int moe_chunk = 0,
+                             bool split = true) {
   PrefillLayout L;
+  const int ms = split ? 16 : 1;
+  auto plan = [&](int n_out, int k, int mode) {
+    return sevo::plan_linear(T, n_out, k, 0, mode, sevo::kLinearMaxMb, ms);
+  };
+  const bool moe = c.n_experts > 0;
+  L.p_qkv = plan((c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim, c.hidden, SEVO_LINEAR_STORE);
+  L.p_o = plan(c.hidden, c.n_q_heads * c.head_dim, SEVO_LINEAR_STORE);
+  if (!moe) {
+    L.p_gu = plan(2 * c.ffn, c.hidden, SEVO_LINEAR_SWIGLU);
+    L.p_d = plan(c.hidden, c.ffn, SEVO_LINEAR_STORE);
+  }
   const size_t H = c.hidden, F = c.ffn, V = c.vocab;
   const size_t qd = (size_t)c.n_q_heads * c.head_dim;
   const size_t qkvd = (size_t)(c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim;
@@ -1072,15 +1100,19 @@ PrefillLayout prefill_layout(const sevo_model_config& c, int T, int R, int moe_c
   L.pos = take(t * 4);
   L.x = take(t * H * 4);
   L.h = take(t16 * H * 2);
-  L.qkv = take(t * qkvd * 4);
+  L.qkv = take(L.p_qkv.k_splits * t * qkvd * 4);
   L.q = take(t * qd * 2);
   L.o = take(t16 * qd * 2);
   L.a = take(t16 * F * 2);
-  L.part = take(c.n_experts > 0 ? t * H * 4 : 0);  // the MoE FFN's output (dense: added in place)
+  // the MoE FFN's output, and the split partials of the output and dense down
+  // projections (in one split they are added to x in place)
+  const int sx = std::max(L.p_o.k_splits, moe ? 1 : L.p_d.k_splits);
+  L.part = take((moe || sx > 1 ? sx : 0) * t * H * 4);
   L.mc = 0;
   L.m_router = L.m_sel = L.m_w = L.m_off = L.m_assign = L.m_act = L.m_slots = L.m_tiles = 0;
   L.m_plan = 0;
-  if (c.n_experts > 0) {
+  L.router_rows = 0;
+  if (moe) {
     size_t mc = moe_chunk > 0 && moe_chunk < kPrefillMoeRows ? round_up(moe_chunk, 16)
                                                               : (size_t)kPrefillMoeRows;
     if (mc > t16) mc = t16;
@@ -1093,7 +1125,8 @@ PrefillLayout prefill_layout(const sevo_model_config& c, int T, int R, int moe_c
     const size_t mc_cap = ((((size_t)1 << 31) - 1) / row_bytes) / 16 * 16;
     if (mc > mc_cap) mc = mc_cap;
     L.mc = (int)mc;
-    L.m_router = take(mc * E * 4);
+    L.router_rows = split ? std::max(mc, std::min(mc, (size_t)4096) * 8) : mc;
+    L.m_router = take(L.router_rows * E * 4);
     L.m_sel = take(mc * kk * 4);
     L.m_w = take(mc * kk * 4);
     L.m_off = take((E + 1) * 4);
@@ -1113,16 +1146,13 @@ PrefillLayout prefill_layout(const sevo_model_config& c, int T, int R, int moe_c
   return L;
 }
 
-// One projection of a prefill: the large-M kernel when it applies, else the
-// decode kernel in one K split (no workspace).  X tiled, or row-major.
-hipError_t prefill_gemm(int m, int n_out, int k, int mode, const sevo::bf16_t* x,
-                        const void* w, void* out, int out_tiled, hipStream_t st,
-                        int x_tiled = 1) {
-  const sevo::bf16_t* wb = static_cast<const sevo::bf16_t*>(w);
-  if (m >= sevo::kLargeGemmMinM && sevo::gemm_large_supported(m, n_out, k))
-    return sevo::launch_gemm_large(m, n_out, k, k, x_tiled, mode, x, wb, out, out_tiled, st);
-  const sevo::LinearPlan p = sevo::plan_linear(m, n_out, k, 1, mode);
-  return sevo::launch_linear(m, n_out, k, k, x_tiled, mode, p, x, wb, out, out_tiled, nullptr, st);
+// A projection of a prefill whose split partials (or whole product) go to out;
+// with one split and add, out += the product.  X tiled, or row-major.
+hipError_t prefill_partials(int m, int n_out, int k, const sevo::LinearPlan& p,
+                            const sevo::bf16_t* x, const void* w, float* out, hipStream_t st,
+                            int add = 0, int x_tiled = 1) {
+  return sevo::launch_linear_partials(m, n_out, k, k, x_tiled, p, x,
+                                      static_cast<const sevo::bf16_t*>(w), out, add, st);
 }
 
 // Entries per expert (n k / E on average) from which a prefill chunk's experts
@@ -1146,12 +1176,14 @@ hipError_t run_moe_prefill_chunk(const sevo_model* m, int l, int c0, int nc,
   int32_t* asg = reinterpret_cast<int32_t*>(ws + L.m_assign);
   float* slots = reinterpret_cast<float*>(ws + L.m_slots);
   int32_t* tiles = reinterpret_cast<int32_t*>(ws + L.m_tiles);
+  const sevo::LinearPlan p_router = sevo::plan_linear(
+      nc, E, H, 0, SEVO_LINEAR_STORE, sevo::kLinearMaxMb, (int)std::min<size_t>(16, L.router_rows / nc));
   const bool grouped = (long long)nc * k >= (long long)kPrefillGroupedMinPerExpert * E;
   hipError_t e;
   {
     ProfScope ps(SEVO_PROF_MOE_ROUTE, st);
-    e = prefill_gemm(nc, E, H, SEVO_LINEAR_STORE, hc, m->w_router[l], rl, 0, st, 0);
-    if (e == hipSuccess) e = sevo::launch_moe_route(rl, 1, nc, E, k, sel, wts, st);
+    e = prefill_partials(nc, E, H, p_router, hc, m->w_router[l], rl, st, 0, 0);
+    if (e == hipSuccess) e = sevo::launch_moe_route(rl, p_router.k_splits, nc, E, k, sel, wts, st);
     if (e == hipSuccess)
       e = sevo::launch_moe_plan(sel, nc * k, E, off, asg, st, grouped ? tiles : nullptr,
                                 reinterpret_cast<int32_t*>(ws + L.m_plan));
@@ -1234,7 +1266,8 @@ SEVO_API sevo_status sevo_prefill_confidence(sevo_model* m, const sevo_prefill_a
   for (int l = 0; l < c.n_layers; ++l)
     if (!a->kv_pools[l] || !aligned16(a->kv_pools[l]))
       return fail(SEVO_ERR_INVALID_ARGUMENT, "layer %d: null or misaligned KV pool", l);
-  const PrefillLayout L = prefill_layout(c, T, R, a->moe_chunk);
+  PrefillLayout L = prefill_layout(c, T, R, a->moe_chunk);
+  if (a->workspace_bytes < L.total) L = prefill_layout(c, T, R, a->moe_chunk, false);
   if (a->workspace_bytes < L.total)
     return fail(SEVO_ERR_WORKSPACE_TOO_SMALL, "prefill needs %zu workspace bytes, got %zu",
                 L.total, a->workspace_bytes);
@@ -1269,25 +1302,26 @@ SEVO_API sevo_status sevo_prefill_confidence(sevo_model* m, const sevo_prefill_a
   if (e != hipSuccess) return hip_fail(e, "prefill (embed)");
   // the output and dense down projections add their product to x in the GEMM
   // epilogue (the same single fp32 add as a separate residual update, without
-  // a round trip of the product through memory); a MoE FFN's slot-order sum
-  // goes to `part`, which the next residual add + RMSNorm adds to x
+  // a round trip of the product through memory); with K split, their partials
+  // go to `part`, as a MoE FFN's slot-order sum does, and the next residual
+  // add + RMSNorm adds them to x
   const bool moe = c.n_experts > 0;
+  int pending = 0;  // partials of the last FFN in `part`, not yet in x
   for (int l = 0; l < c.n_layers; ++l) {
     {
       ProfScope ps(SEVO_PROF_NORM, st);
-      const bool add_part = l > 0 && moe;
-      e = sevo::launch_add_rmsnorm(x, add_part ? part : nullptr, add_part ? 1 : 0,
+      e = sevo::launch_add_rmsnorm(x, pending ? part : nullptr, pending,
                                    static_cast<const sevo::bf16_t*>(m->attn_norm[l]), T, H,
                                    c.rms_eps, h, st);
     }
     if (e == hipSuccess) {
       ProfScope ps(SEVO_PROF_QKV, st);
-      e = prefill_gemm(T, qkvd, H, SEVO_LINEAR_STORE, h, m->w_qkv[l], qkv, 0, st);
+      e = prefill_partials(T, qkvd, H, L.p_qkv, h, m->w_qkv[l], qkv, st);
     }
     if (e == hipSuccess) {
       ProfScope ps(SEVO_PROF_ROPE_APPEND, st);
       sevo::RopeAppendArgs r;
-      fill_rope_args(m, l, qkv, 1, T, pos, a->page_table, a->max_pages, a->num_pages, q,
+      fill_rope_args(m, l, qkv, L.p_qkv.k_splits, T, pos, a->page_table, a->max_pages, a->num_pages, q,
                      a->kv_pools[l], r);
       r.row_of_token = row;
       e = sevo::launch_qk_norm_rope_append(r, st);
@@ -1302,13 +1336,14 @@ SEVO_API sevo_status sevo_prefill_confidence(sevo_model* m, const sevo_prefill_a
       pa.scale = scale; pa.out = o; pa.out_tiled = 1; pa.total_tokens = T;
       e = sevo::launch_attn_prefill(pa, st);
     }
+    const int so = L.p_o.k_splits > 1 ? L.p_o.k_splits : 0;
     if (e == hipSuccess) {
       ProfScope ps(SEVO_PROF_ATTN_OUT, st);
-      e = prefill_gemm(T, H, qd, SEVO_LINEAR_ADD, o, m->w_o[l], x, 0, st);
+      e = prefill_partials(T, H, qd, L.p_o, o, m->w_o[l], so ? part : x, st, so ? 0 : 1);
     }
     if (e == hipSuccess) {
       ProfScope ps(SEVO_PROF_NORM, st);
-      e = sevo::launch_add_rmsnorm(x, nullptr, 0, static_cast<const sevo::bf16_t*>(m->ffn_norm[l]),
+      e = sevo::launch_add_rmsnorm(x, so ? part : nullptr, so, static_cast<const sevo::bf16_t*>(m->ffn_norm[l]),
                                    T, H, c.rms_eps, h, st, nullptr, 0, moe ? 0 : 1);
     }
     if (moe) {
@@ -1318,14 +1353,19 @@ SEVO_API sevo_status sevo_prefill_confidence(sevo_model* m, const sevo_prefill_a
         const int nc = T - c0 < L.mc ? T - c0 : L.mc;
         e = run_moe_prefill_chunk(m, l, c0, nc, h, ws, L, part, st);
       }
+      pending = 1;
     } else {
       if (e == hipSuccess) {
         ProfScope ps(SEVO_PROF_GATE_UP, st);
-        e = prefill_gemm(T, 2 * F, H, SEVO_LINEAR_SWIGLU, h, m->w_gate_up[l], act, 1, st);
+        e = sevo::launch_linear(T, 2 * F, H, H, 1, SEVO_LINEAR_SWIGLU, L.p_gu, h,
+                                static_cast<const sevo::bf16_t*>(m->w_gate_up[l]), act, 1,
+                                nullptr, st);
       }
+      pending = L.p_d.k_splits > 1 ? L.p_d.k_splits : 0;
       if (e == hipSuccess) {
         ProfScope ps(SEVO_PROF_DOWN, st);
-        e = prefill_gemm(T, H, F, SEVO_LINEAR_ADD, act, m->w_down[l], x, 0, st);
+        e = prefill_partials(T, H, F, L.p_d, act, m->w_down[l], pending ? part : x, st,
+                             pending ? 0 : 1);
       }
     }
     if (e != hipSuccess) return hip_fail(e, "prefill (layer)");
@@ -1336,13 +1376,15 @@ SEVO_API sevo_status sevo_prefill_confidence(sevo_model* m, const sevo_prefill_a
     const int nr = R - r0 < L.rc ? R - r0 : L.rc;
     {
       ProfScope ps(SEVO_PROF_NORM, st);
-      e = sevo::launch_add_rmsnorm(x, moe ? part : nullptr, moe ? 1 : 0,
+      e = sevo::launch_add_rmsnorm(x, pending ? part : nullptr, pending,
                                    static_cast<const sevo::bf16_t*>(m->final_norm), nr, H,
                                    c.rms_eps, hf, st, a->scored_rows + r0, T);
     }
     if (e == hipSuccess) {
       ProfScope ps(SEVO_PROF_LM_HEAD, st);
-      e = prefill_gemm(nr, c.vocab, H, SEVO_LINEAR_STORE, hf, m->lm_head, logits, 0, st);
+      const sevo::LinearPlan p_lm = sevo::plan_linear(nr, c.vocab, H, 1, SEVO_LINEAR_STORE,
+                                                      sevo::kLinearMaxMb, 1);
+      e = prefill_partials(nr, c.vocab, H, p_lm, hf, m->lm_head, logits, st);
     }
     if (e == hipSuccess) {
       ProfScope ps(SEVO_PROF_SAMPLE, st);

@@ -496,8 +496,8 @@ LINEAR_CASES = [
     (64, 24576, 4096, 2, 0, 1), (16, 4096, 4096, 1, 0, 0), (100, 128, 256, 0, 2, 1),
     # k not a multiple of 128: per-wave step counts differ, short tails
     (5, 128, 96, 0, 0, 0), (20, 256, 160, 1, 0, 1), (3, 128, 32, 2, 0, 1), (40, 192, 352, 0, 2, 0),
-    # m >= 256 with k % 64 == 0: the large-M kernel (256 x 256 tiles, 64-k
-    # stages); one exact tile, ragged m and n tails, row-major X, prefill shapes
+    # more than 64 rows: the tiled kernel; exact tiles, ragged m and n tails,
+    # row-major X, prefill shapes
     (256, 256, 64, 0, 0, 1), (300, 320, 128, 0, 0, 1), (777, 448, 192, 1, 0, 0),
     (513, 640, 256, 2, 0, 1), (1024, 6144, 4096, 0, 0, 1), (1000, 4096, 12288, 1, 0, 1),
     (600, 2048, 1024, 2, 0, 0), (255, 128, 64, 0, 0, 1),
@@ -589,6 +589,58 @@ def test_linear_matches_float64_matmul(S, m, n_out, k, mode, ks, xt):
     got = out.double().cpu().numpy()
     scale = np.sqrt(k) * 0.02
     np.testing.assert_allclose(got, ref, rtol=0, atol=2e-5 * scale + 1e-6 * np.abs(ref).max())
+
+
+# shapes on either side of the tile dispatch: each tile (128 x 128 with k % 64
+# == 0, 128 x 256, 192 x 256, 256 x 256), ragged last rows and columns, K splits
+# with a short last one, the eight-block skinny kernel, k % 64 == 32
+TILE_CASES = [
+    # m, n_out, k, mode, x_tiled
+    (65, 192, 64, 0, 1), (128, 320, 192, 2, 0), (129, 192, 4160, 0, 1), (130, 128, 4160, 1, 0),
+    (70, 512, 96, 0, 0), (200, 320, 1056, 1, 1), (255, 576, 160, 2, 0),
+    (300, 24640, 64, 0, 1), (193, 24640, 128, 2, 0), (500, 24640, 64, 1, 0),
+    (512, 24640, 96, 2, 1), (257, 192, 2080, 1, 1),
+    (100, 24576, 1408, 2, 1), (128, 24576, 1408, 2, 0),
+]
+
+
+@pytest.mark.parametrize("m,n_out,k,mode,xt", TILE_CASES)
+def test_linear_tiles_at_their_edges(S, m, n_out, k, mode, xt):
+    """The tiled and eight-block kernels against float64 products on a random
+    8th of the columns and every row; with too small a workspace, the plans
+    without one (or with 64-row tiles) give the same product."""
+    sevo, _ = S
+    say(f"linear tiles m={m} n={n_out} k={k} mode={mode} x_tiled={xt}")
+    x, _, wp, xh, wh = _linear_inputs(sevo, m, n_out, k, mode)
+    if xt:
+        xb = tile_activations_host(bf16_bits(x).reshape(m, k))
+        x = torch.from_numpy(xb.view(np.int16)).cuda().view(torch.bfloat16)
+    F = n_out // 2 if mode == 2 else n_out
+    cols = np.sort(np.random.default_rng(m).choice(F, max(64, F // 8), replace=False))
+    cols[-1] = F - 1
+    xd = xh.astype(np.float64)
+    y = xd @ wh[cols].astype(np.float64).T
+    if mode == 2:
+        y = od.silu(y) * (xd @ wh[F + cols].astype(np.float64).T)
+    base = 0.25 if mode == 1 else 0.0
+    need = sevo.sevo_linear_workspace_bytes(m, n_out, k)
+    for nbytes in (need, need - 256 if m < 256 else 0):
+        ws = poisoned(nbytes)[:max(nbytes, 256)]
+        out = (None if mode == 2 else
+               torch.full((m, n_out), base, dtype=torch.float32, device="cuda"))
+        try:
+            out = sevo.sevo_linear(x, wp, mode=mode, m=m, x_tiled=bool(xt), out=out, workspace=ws)
+        except sevo.SevoError as e:   # below 256 rows, more than 64-row tiles have room for
+            assert m < 256 and nbytes < need and e.status == sevo.WORKSPACE_TOO_SMALL
+            continue
+        torch.cuda.synchronize()
+        got = out.double().cpu().numpy()[:, cols]
+        if mode == 2:
+            # one bf16 rounding of the product plus fp32 accumulation error
+            assert np.all(np.abs(got - y) <= 2 ** -8 * np.abs(y) + 1e-4 * np.abs(y).max())
+        else:
+            np.testing.assert_allclose(got, base + y, rtol=0,
+                                       atol=2e-5 * np.sqrt(k) * 0.02 + 1e-6 * np.abs(y).max())
 
 
 # one shape per instantiated skinny kernel: (M tile rows, 16-row weight blocks

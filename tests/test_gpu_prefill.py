@@ -11,7 +11,8 @@ import torch
 
 from oracle import decoder as od
 from paper_2604_07725_amd import synth
-from tests.gpu_helpers import ATTN_REL_TOL, attn_rel_err, make_population, say, to_np
+from tests.gpu_helpers import (ATTN_REL_TOL, attn_rel_err, make_population, poisoned, say,
+                               to_np)
 
 pytestmark = pytest.mark.gpu
 
@@ -413,6 +414,31 @@ def test_attn_prefill_absent_pages_contribute_no_keys(S, dims):
             worst = max(worst, attn_rel_err(row, ref))
     say(f"  worst rel err {worst:.2e}")
     assert worst <= min(ATTN_REL_TOL, 8e-3)
+
+
+@pytest.mark.parametrize("workload", ["tiny_step", "tiny_moe_step"])
+def test_prefill_confidence_without_room_for_split_partials(S, workload):
+    """A workspace without room for the projections' split partials is accepted
+    and gives the same confidences (to a flip of a bf16 storage point)."""
+    sevo, di = S
+    shape = synth.WORKLOADS[workload].shape
+    pop = make_population([300, 40], seed=2)
+    model = sevo.sevo_init_model(shape, di.device_weights(shape, 2), max_position=301)
+    T, rows = 340, torch.arange(20, 340, dtype=torch.int32, device="cuda")
+    toks = torch.arange(T, dtype=torch.int32, device="cuda") * 7 % shape.vocab
+    ss = torch.tensor([0, 300, 340], dtype=torch.int32, device="cuda")
+    pt = torch.from_numpy(pop.page_table.astype(np.int32)).cuda()
+    need = sevo.sevo_prefill_workspace_bytes(model, T, 320)
+    got = []
+    for nbytes in (need, need - 256):
+        buf = sevo.PrefillBuffers(model, toks, ss, pt, di.device_pools(shape, 2, pop.n_pages),
+                                  rows, 20, 300, workspace=poisoned(nbytes))
+        buf.run()
+        torch.cuda.synchronize()
+        got.append(buf.out_row_conf.cpu().numpy())
+    assert np.isfinite(got[0]).all()
+    assert np.abs(got[0] - got[1]).max() <= 2e-2   # the oracle bar of the tiny model's rows
+    model.close()
 
 
 def test_prefill_confidence_rejects_a_short_max_seq_len(S):
