@@ -33,8 +33,8 @@
 // gate/up matrix packed in 32 + 32 row superblocks (bf16 output, tiled or
 // row-major).
 //
-// Grouped form (the mixture of experts of a prefill): the m-tiles are 256-entry
-// tiles of the experts' entry lists (tile_off from the planner), a tile's
+// Grouped form (the mixture of experts of a prefill): the m-tiles are tiles of
+// BM entries of the experts' lists (tile_off from the planner), a tile's
 // weights are its expert's, and its A rows are gathered per lane: the entry's
 // token row of the normed input (gate/up), or the expert's SwiGLU rows (down).
 // Both are row-major: a row's 32 columns of a stage are 64 consecutive bytes
@@ -97,9 +97,13 @@ gemm_large_kernel(const bf16_t* __restrict__ X, int ldx, int M, const bf16_t* __
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / WN, wn = wave % WN;
 
-  // ---- tile order: XCD-contiguous ranges, groups of GM m-tiles
+  // ---- tile order: XCD-contiguous ranges, groups of GM m-tiles.  Grouped: of
+  // the tiles that the entry lists fill (the grid has room for a part-filled
+  // tile per expert more; dividing that among the XCDs left the last ones idle)
+  if constexpr (GR) tiles_m = g.tile_off[g.E];
   const int total = tiles_m * tiles_n;
   int t = blockIdx.x;
+  if (GR && t >= total) return;  // uniform over the workgroup, before any barrier
   {
     const int per = total >> 3;  // full rounds of 8
     if (t < per * 8) t = (t & 7) * per + (t >> 3);
@@ -117,9 +121,7 @@ gemm_large_kernel(const bf16_t* __restrict__ X, int ldx, int M, const bf16_t* __
   int rows = M;      // rows of this tile's matrix (the expert's entries)
   int ent0 = 0;      // first entry of the expert
   if constexpr (GR) {
-    const int total_m = g.tile_off[g.E];
-    if (tm >= total_m) return;  // uniform over the workgroup, before any barrier
-    int lo = 0, hi = g.E;       // tile_off[lo] <= tm < tile_off[hi]
+    int lo = 0, hi = g.E;  // tile_off[lo] <= tm < tile_off[hi]
     while (hi - lo > 1) {
       const int mid = (lo + hi) >> 1;
       if (g.tile_off[mid] <= tm) lo = mid;
@@ -432,7 +434,7 @@ struct LgTile {
   int bm, bn;
   double per_1024;
 };
-const LgTile kTiles[] = {{256, 256, 22.0}, {192, 256, 18.5}, {128, 256, 13.0}, {128, 128, 7.8}};
+const LgTile kTiles[] = {{256, 256, 23.5}, {192, 256, 18.5}, {128, 256, 13.0}, {128, 128, 7.8}};
 constexpr int kNumTiles = 4;
 constexpr double kTileFixed = 8.0;     // us per tile
 constexpr double kPartialPerMB = 0.4;  // us per MB of split partials, written and read back
@@ -491,11 +493,23 @@ hipError_t launch_gemm_large(int m, int n_out, int k, int ldx, int x_tiled, int 
   }
 }
 
+// The rows of a grouped tile from the entries per expert (30B-A3B shape, us of
+// a layer's experts with tiles of 64 / 128 / 256 rows: 31 entries each 273 / 268
+// / 284, 62 each 330 / 299 / 315, 125 each 462 / 404 / 372, 250 each 767 / 615 /
+// 622, 509 each 1426 / 1114 / 1032): half a tile per expert is padding, but the
+// larger tile does more per byte.
+int moe_group_rows(long long entries, int n_experts) {
+  return entries < 96ll * n_experts ? 128 : 256;
+}
+
 hipError_t launch_gemm_grouped(int down, int m, int n_out, int k, const bf16_t* x,
-                               const bf16_t* w, void* out, const GroupArgs& g, int max_tiles_m,
-                               hipStream_t st) {
+                               const bf16_t* w, void* out, const GroupArgs& g, int tile_rows,
+                               int max_tiles_m, hipStream_t st) {
   if (m == 0 || max_tiles_m == 0) return hipSuccess;
   const LgArgs a{m, n_out, k, k, 1, k, x, w, out, 0, st};
+  if (tile_rows == 128)
+    return down ? run_lg<128, 256, 8, 1, 3, 0, 1>(a, max_tiles_m, g)
+                : run_lg<128, 256, 8, 1, 2, 0, 1>(a, max_tiles_m, g);
   return down ? run_lg<256, 256, 8, 1, 3, 0, 1>(a, max_tiles_m, g)
               : run_lg<256, 256, 8, 1, 2, 0, 1>(a, max_tiles_m, g);
 }

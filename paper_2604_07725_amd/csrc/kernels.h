@@ -91,7 +91,8 @@ struct PrefillAttnArgs {
 hipError_t launch_attn_prefill(const PrefillAttnArgs& a, hipStream_t st);
 
 // ---- moe.hip: mixture-of-experts FFN of a decode step
-constexpr int kMoeGroupRows = 256;  // rows per tile of the grouped large-M GEMM
+// entries per tile of the grouped GEMM (128 or 256)
+int moe_group_rows(long long entries, int n_experts);
 
 struct MoeExpertArgs {
   int n, hidden, ffn, n_experts, top_k;
@@ -113,11 +114,12 @@ hipError_t launch_moe_route(const float* part, int S, int n, int E, int k, int32
 hipError_t launch_moe_sum_slots(const float* part, int k, int n, int H, float* out,
                                 hipStream_t st);
 // offsets [E + 1], assign [nk] (entries expert-major, token order); with
-// tile_off [E + 1]: each expert's first 256-entry tile (grouped GEMM)
+// tile_off [E + 1]: each expert's first tile of tile_rows entries (grouped GEMM)
 // scratch (optional, moe_plan_scratch_bytes): from 4097 entries the plan runs
 // as three launches over 1024-entry chunks instead of one workgroup
 hipError_t launch_moe_plan(const int32_t* sel, int nk, int E, int32_t* offsets, int32_t* assign,
-                           hipStream_t st, int32_t* tile_off = nullptr, int32_t* scratch = nullptr);
+                           hipStream_t st, int32_t* tile_off = nullptr, int tile_rows = 256,
+                           int32_t* scratch = nullptr);
 size_t moe_plan_scratch_bytes(int nk, int E);
 // gate/up + SwiGLU into act, then down into part
 hipError_t launch_moe_experts(const MoeExpertArgs& a, hipStream_t st);
@@ -156,8 +158,8 @@ constexpr int kTileMinM = 65;
 // from here on a caller's k_splits is not taken and no workspace is required
 constexpr int kLargeGemmMinM = 256;
 LinearPlan plan_tiles(int m, int n_out, int k, int mode, int fixed_splits, int max_splits);
-// grouped form (mixture of experts): m-tiles are 256-entry tiles of the
-// experts' entry lists; the expert's weights at w + e n_out k
+// grouped form (mixture of experts): m-tiles are tiles of tile_rows entries of
+// the experts' lists; the expert's weights at w + e n_out k
 struct GroupArgs {
   const int32_t* offsets = nullptr;   // [E + 1] entry offsets
   const int32_t* assign = nullptr;    // [n k] entries t * k + slot
@@ -169,10 +171,10 @@ struct GroupArgs {
 //   out bf16 act [n k][n_out / 2] at the entry positions (SwiGLU);
 // down 1: x = act [n k][k] row-major (m = n k entries), out fp32
 //   [k slots][n][n_out] = weight * product.  max_tiles_m >= sum of the
-//   experts' tile counts (n k / 256 + E).
+//   experts' tile counts (n k / tile_rows + E).
 hipError_t launch_gemm_grouped(int down, int m, int n_out, int k, const bf16_t* x,
-                               const bf16_t* w, void* out, const GroupArgs& g, int max_tiles_m,
-                               hipStream_t st);
+                               const bf16_t* w, void* out, const GroupArgs& g, int tile_rows,
+                               int max_tiles_m, hipStream_t st);
 hipError_t launch_gemm_large(int m, int n_out, int k, int ldx, int x_tiled, int mode,
                              const LinearPlan& plan, const bf16_t* x, const bf16_t* w, void* out,
                              int out_tiled, hipStream_t st);

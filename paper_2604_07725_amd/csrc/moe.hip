@@ -143,7 +143,8 @@ __global__ __launch_bounds__(kPlanThreads) void moe_plan_kernel(const int32_t* _
                                                                 int nk, int E,
                                                                 int32_t* __restrict__ offsets,
                                                                 int32_t* __restrict__ assign,
-                                                                int32_t* __restrict__ tile_off) {
+                                                                int32_t* __restrict__ tile_off,
+                                                                int tile_rows) {
   __shared__ int cnt[kMoeMaxExperts];
   __shared__ int base[kMoeMaxExperts];
   __shared__ uint32_t bits[kMoeMaxExperts][kPlanWords];
@@ -157,14 +158,14 @@ __global__ __launch_bounds__(kPlanThreads) void moe_plan_kernel(const int32_t* _
   __syncthreads();
   if (tid < 64) {
     // exclusive prefixes over the experts (lane j scans experts 4j..4j+3,
-    // E <= 256): entry offsets, and (tile_off) the first 256-entry tile of
+    // E <= 256): entry offsets, and (tile_off) the first tile (of tile_rows entries) of
     // each expert for the grouped large-M GEMM
     int v[4], tv[4], sum = 0, tsum = 0;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int e = 4 * tid + u;
       v[u] = e < E ? cnt[e] : 0;
-      tv[u] = (v[u] + kMoeGroupRows - 1) / kMoeGroupRows;
+      tv[u] = (v[u] + tile_rows - 1) / tile_rows;
       sum += v[u];
       tsum += tv[u];
     }
@@ -242,7 +243,7 @@ __global__ __launch_bounds__(kPlanThreads) void moe_plan_count_kernel(
 // walks a quarter of the chunks (E <= 256).
 __global__ __launch_bounds__(kPlanThreads) void moe_plan_scan_kernel(
     int32_t* __restrict__ ccnt, int chunks, int E, int32_t* __restrict__ offsets,
-    int32_t* __restrict__ tile_off) {
+    int32_t* __restrict__ tile_off, int tile_rows) {
   constexpr int kParts = kPlanThreads / kMoeMaxExperts;
   __shared__ int psum[kParts][kMoeMaxExperts];
   __shared__ int ebase[kMoeMaxExperts];
@@ -257,7 +258,7 @@ __global__ __launch_bounds__(kPlanThreads) void moe_plan_scan_kernel(
   __syncthreads();
   if (tid < 64) {
     // exclusive prefixes over the experts (lane j: experts 4j..4j+3): entry
-    // offsets and the first 256-entry tile of each expert
+    // offsets and the first tile (of tile_rows entries) of each expert
     int v[4], tv[4], tot = 0, ttot = 0;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -266,7 +267,7 @@ __global__ __launch_bounds__(kPlanThreads) void moe_plan_scan_kernel(
       if (x < E)
 #pragma unroll
         for (int q = 0; q < kParts; ++q) v[u] += psum[q][x];
-      tv[u] = (v[u] + kMoeGroupRows - 1) / kMoeGroupRows;
+      tv[u] = (v[u] + tile_rows - 1) / tile_rows;
       tot += v[u];
       ttot += tv[u];
     }
@@ -522,21 +523,21 @@ hipError_t launch_moe_route(const float* part, int S, int n, int E, int k, int32
 }
 
 hipError_t launch_moe_plan(const int32_t* sel, int nk, int E, int32_t* offsets, int32_t* assign,
-                           hipStream_t st, int32_t* tile_off, int32_t* scratch) {
+                           hipStream_t st, int32_t* tile_off, int tile_rows, int32_t* scratch) {
   if (scratch && nk > 4 * kPlanThreads) {
     const int chunks = (nk + kPlanThreads - 1) / kPlanThreads;
     hipLaunchKernelGGL(moe_plan_count_kernel, dim3(chunks), dim3(kPlanThreads), 0, st, sel, nk, E,
                        scratch);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     hipLaunchKernelGGL(moe_plan_scan_kernel, dim3(1), dim3(kPlanThreads), 0, st, scratch, chunks,
-                       E, offsets, tile_off);
+                       E, offsets, tile_off, tile_rows);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     hipLaunchKernelGGL(moe_plan_place_kernel, dim3(chunks), dim3(kPlanThreads), 0, st, sel, nk, E,
                        scratch, assign);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(moe_plan_kernel, dim3(1), dim3(kPlanThreads), 0, st, sel, nk, E, offsets,
-                     assign, tile_off);
+                     assign, tile_off, tile_rows);
   return hipGetLastError();
 }
 

@@ -1156,13 +1156,14 @@ hipError_t prefill_partials(int m, int n_out, int k, const sevo::LinearPlan& p,
 }
 
 // Entries per expert (n k / E on average) from which a prefill chunk's experts
-// run as grouped large-M GEMMs (256-entry tiles, each expert's weights read
-// once per tile) instead of the decode kernels (16-64-row tiles).
-constexpr int kPrefillGroupedMinPerExpert = 32;
+// run as grouped large-M GEMMs (128- or 256-entry tiles, each expert's
+// weights read once per tile) instead of the decode kernels (16-64-row tiles).
+constexpr int kPrefillGroupedMinPerExpert = 24;
 
 // The MoE FFN of prefill rows c0 .. c0 + nc (c0 a multiple of 16) on the
-// row-major normed input h (the experts gather its rows): router GEMM, top-k, entry lists, expert gate/up + down into
-// per-slot outputs, then part[c0 + i] = their slot-order sum.
+// row-major normed input h (the experts gather its rows): router GEMM, top-k,
+// entry lists, expert gate/up + down into per-slot outputs, then part[c0 + i] =
+// their slot-order sum.
 hipError_t run_moe_prefill_chunk(const sevo_model* m, int l, int c0, int nc,
                                  const sevo::bf16_t* h, char* ws, const PrefillLayout& L,
                                  float* part, hipStream_t st) {
@@ -1179,13 +1180,14 @@ hipError_t run_moe_prefill_chunk(const sevo_model* m, int l, int c0, int nc,
   const sevo::LinearPlan p_router = sevo::plan_linear(
       nc, E, H, 0, SEVO_LINEAR_STORE, sevo::kLinearMaxMb, (int)std::min<size_t>(16, L.router_rows / nc));
   const bool grouped = (long long)nc * k >= (long long)kPrefillGroupedMinPerExpert * E;
+  const int tile_rows = sevo::moe_group_rows((long long)nc * k, E);
   hipError_t e;
   {
     ProfScope ps(SEVO_PROF_MOE_ROUTE, st);
     e = prefill_partials(nc, E, H, p_router, hc, m->w_router[l], rl, st, 0, 0);
     if (e == hipSuccess) e = sevo::launch_moe_route(rl, p_router.k_splits, nc, E, k, sel, wts, st);
     if (e == hipSuccess)
-      e = sevo::launch_moe_plan(sel, nc * k, E, off, asg, st, grouped ? tiles : nullptr,
+      e = sevo::launch_moe_plan(sel, nc * k, E, off, asg, st, grouped ? tiles : nullptr, tile_rows,
                                 reinterpret_cast<int32_t*>(ws + L.m_plan));
   }
   if (e != hipSuccess) return e;
@@ -1194,15 +1196,15 @@ hipError_t run_moe_prefill_chunk(const sevo_model* m, int l, int c0, int nc,
     sevo::GroupArgs g;
     g.offsets = off; g.assign = asg; g.tile_off = tiles; g.weights = wts;
     g.E = E; g.k = k; g.n = nc;
-    const int max_tiles = (nc * k + sevo::kMoeGroupRows - 1) / sevo::kMoeGroupRows + E;
+    const int max_tiles = (nc * k + tile_rows - 1) / tile_rows + E;
     sevo::bf16_t* act = reinterpret_cast<sevo::bf16_t*>(ws + L.m_act);
     e = sevo::launch_gemm_grouped(0, nc, 2 * c.expert_ffn, H, hc,
                                   static_cast<const sevo::bf16_t*>(m->w_expert_gate_up[l]), act,
-                                  g, max_tiles, st);
+                                  g, tile_rows, max_tiles, st);
     if (e == hipSuccess)
       e = sevo::launch_gemm_grouped(1, nc * k, H, c.expert_ffn, act,
                                     static_cast<const sevo::bf16_t*>(m->w_expert_down[l]), slots,
-                                    g, max_tiles, st);
+                                    g, tile_rows, max_tiles, st);
     if (e == hipSuccess)
       e = sevo::launch_moe_sum_slots(slots, k, nc, H, part + (size_t)c0 * H, st);
     return e;
