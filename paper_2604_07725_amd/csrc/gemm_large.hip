@@ -222,6 +222,9 @@ gemm_large_kernel(const bf16_t* __restrict__ X, int ldx, int M, const bf16_t* __
   const int b_off = (FA + wn * 4 + half) * 512 + r16 * 8 + khi * 128;
 
   constexpr int H = 2 * KSUB;  // 16-k MFMA groups of a stage
+  // TR: the weights as the MFMA's A operand, so that a lane holds four
+  // consecutive columns of one row (one store of a run instead of four)
+  constexpr bool TR = EPI == 2;
   struct Frags {
     bf16x8v a[MT], b[2];
   };
@@ -240,7 +243,8 @@ gemm_large_kernel(const bf16_t* __restrict__ X, int ldx, int M, const bf16_t* __
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
       for (int nt = 0; nt < 2; ++nt)
-        acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[mt], f.b[nt], acc[mt][nt], 0, 0, 0);
+        acc[mt][nt] = TR ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.b[nt], f.a[mt], acc[mt][nt], 0, 0, 0)
+                         : __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[mt], f.b[nt], acc[mt][nt], 0, 0, 0);
   };
 
   // Pipeline: up to three stages of direct loads are in flight while one is
@@ -292,6 +296,7 @@ gemm_large_kernel(const bf16_t* __restrict__ X, int ldx, int M, const bf16_t* __
 
   // ---- epilogue.  Accumulator element e of tile (mt, nt): row
   // 8 (e / 4) + 4 (lane / 32) + e % 4, column lane % 32.
+  // (TR: row lane % 32, column 8 (e / 4) + 4 (lane / 32) + e % 4.)
   const int col_l = lane & 31;
   auto row_of = [&](int mt, int e) {
     return m0 + (wm * MT + mt) * 32 + 8 * (e >> 2) + 4 * khi + (e & 3);
@@ -300,20 +305,24 @@ gemm_large_kernel(const bf16_t* __restrict__ X, int ldx, int M, const bf16_t* __
     const int F = N >> 1;
     const int sbg = (n0 >> 6) + wn;
     if (sbg <= last_sb) {
-      const int f = sbg * 32 + col_l;
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
+      for (int mt = 0; mt < MT; ++mt) {
+        const int row = m0 + (wm * MT + mt) * 32 + col_l;
+        if (row >= rows) continue;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int row = row_of(mt, e);
-          if (row < rows) {
-            const float gt = acc[mt][0][e], u = acc[mt][1][e];
-            const float v = gt / (1.f + __expf(-gt)) * u;
-            const size_t off =
-                out_tiled ? act_tile_offset(row, f, F) : (size_t)(ent0 + row) * F + f;
-            out_bf16[off] = f32_to_bf16(v);
+        for (int q = 0; q < 4; ++q) {
+          const int f = sbg * 32 + 8 * q + 4 * khi;
+          float v[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float gt = acc[mt][0][4 * q + e], u = acc[mt][1][4 * q + e];
+            v[e] = gt / (1.f + __expf(-gt)) * u;
           }
+          const uint2 o = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+          const size_t off = out_tiled ? act_tile_offset(row, f, F) : (size_t)(ent0 + row) * F + f;
+          *reinterpret_cast<uint2*>(out_bf16 + off) = o;
         }
+      }
     }
   } else if constexpr (EPI == 3) {
     // grouped down: row = entry ent0 + row of the expert -> (token, slot).
