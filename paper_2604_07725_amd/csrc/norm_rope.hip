@@ -394,16 +394,17 @@ __global__ __launch_bounds__(1024) void add_rmsnorm_kernel(float* __restrict__ x
   }
 }
 
-// The same for many rows with at most one partial (a prefill): 256 threads
-// per row, so eight rows per CU are in flight instead of two, and thread t
-// keeps the 4-column groups 1024 g + 4 t (g < NG) in registers across the
+// The same for many rows (a prefill): 256 threads per row, so eight rows per CU
+// are in flight instead of two, the partials' loads in groups of four, and
+// thread t keeps the 4-column groups 1024 g + 4 t (g < NG) in registers across the
 // reduction.  The sum of squares is formed exactly as in the 1024-thread form:
 // the groups of its thread T = 256 (g % 4) + t in order, one wave sum per
 // wave of T, the 16 wave sums in order, so both forms give identical output.
 template <int NG>
 __global__ __launch_bounds__(256) void add_rmsnorm_rows_kernel(float* __restrict__ x,
                                                                const float* __restrict__ part,
-                                                               int S, const bf16_t* __restrict__ gain,
+                                                               int S, size_t part_stride,
+                                                               const bf16_t* __restrict__ gain,
                                                                int cols, float eps,
                                                                bf16_t* __restrict__ out,
                                                                int out_tiled,
@@ -421,19 +422,27 @@ __global__ __launch_bounds__(256) void add_rmsnorm_rows_kernel(float* __restrict
     if (c < cols) v[g] = *reinterpret_cast<const f32x4*>(xr + c);
   }
   if (S > 0) {
-    f32x4 p[NG];
+    constexpr int kAtOnce = NG > 4 ? 2 : 4;  // partials loaded together, added in order
+    for (int s0 = 0; s0 < S; s0 += kAtOnce) {
+      f32x4 p[kAtOnce][NG];
 #pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      const int c = 1024 * g + 4 * t;
-      if (c < cols) p[g] = *reinterpret_cast<const f32x4*>(pr + c);
+      for (int j = 0; j < kAtOnce; ++j)
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+          const int c = 1024 * g + 4 * t;
+          if (s0 + j < S && c < cols)
+            p[j][g] = *reinterpret_cast<const f32x4*>(pr + (s0 + j) * part_stride + c);
+        }
+#pragma unroll
+      for (int j = 0; j < kAtOnce; ++j)
+#pragma unroll
+        for (int g = 0; g < NG; ++g)
+          if (s0 + j < S) v[g] += p[j][g];
     }
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
       const int c = 1024 * g + 4 * t;
-      if (c < cols) {
-        v[g] += p[g];
-        if (!row_idx) *reinterpret_cast<f32x4*>(xr + c) = v[g];
-      }
+      if (c < cols && !row_idx) *reinterpret_cast<f32x4*>(xr + c) = v[g];
     }
   }
   float acc[4] = {0.f, 0.f, 0.f, 0.f};
@@ -474,11 +483,11 @@ hipError_t launch_add_rmsnorm(float* x, const float* part, int S, const bf16_t* 
   if (S > 16) return hipErrorInvalidValue;
   const size_t stride = (size_t)(row_idx ? part_rows : rows) * cols;
   const int s_eff = part ? S : 0;
-  if (rows >= 512 && s_eff <= 1 && cols <= 8192) {
+  if (rows >= 512 && cols <= 8192) {
     const int ng = (cols + 1023) / 1024;
     auto go = [&](auto kern) {
-      hipLaunchKernelGGL(kern, dim3(rows), dim3(256), 0, st, x, part, s_eff, gain, cols, eps,
-                         out, out_tiled, row_idx);
+      hipLaunchKernelGGL(kern, dim3(rows), dim3(256), 0, st, x, part, s_eff, stride, gain,
+                         cols, eps, out, out_tiled, row_idx);
     };
     if (ng <= 2) go(add_rmsnorm_rows_kernel<2>);
     else if (ng <= 4) go(add_rmsnorm_rows_kernel<4>);

@@ -1162,8 +1162,8 @@ constexpr int kPrefillGroupedMinPerExpert = 24;
 
 // The MoE FFN of prefill rows c0 .. c0 + nc (c0 a multiple of 16) on the
 // row-major normed input h (the experts gather its rows): router GEMM, top-k,
-// entry lists, expert gate/up + down into per-slot outputs, then part[c0 + i] =
-// their slot-order sum.
+// entry lists, expert gate/up + down into per-slot outputs, then (with part)
+// part[c0 + i] = their slot-order sum.
 hipError_t run_moe_prefill_chunk(const sevo_model* m, int l, int c0, int nc,
                                  const sevo::bf16_t* h, char* ws, const PrefillLayout& L,
                                  float* part, hipStream_t st) {
@@ -1206,7 +1206,7 @@ hipError_t run_moe_prefill_chunk(const sevo_model* m, int l, int c0, int nc,
                                     static_cast<const sevo::bf16_t*>(m->w_expert_down[l]), slots,
                                     g, tile_rows, max_tiles, st);
     if (e == hipSuccess)
-      e = sevo::launch_moe_sum_slots(slots, k, nc, H, part + (size_t)c0 * H, st);
+      e = part ? sevo::launch_moe_sum_slots(slots, k, nc, H, part + (size_t)c0 * H, st) : hipSuccess;
     return e;
   }
   sevo::MoeExpertArgs ma;
@@ -1220,7 +1220,8 @@ hipError_t run_moe_prefill_chunk(const sevo_model* m, int l, int c0, int nc,
   ma.act = reinterpret_cast<sevo::bf16_t*>(ws + L.m_act);
   ma.part = slots;
   e = sevo::launch_moe_experts(ma, st);
-  if (e == hipSuccess) e = sevo::launch_moe_sum_slots(slots, k, nc, H, part + (size_t)c0 * H, st);
+  if (e == hipSuccess && part)
+    e = sevo::launch_moe_sum_slots(slots, k, nc, H, part + (size_t)c0 * H, st);
   return e;
 }
 
@@ -1306,13 +1307,17 @@ SEVO_API sevo_status sevo_prefill_confidence(sevo_model* m, const sevo_prefill_a
   // epilogue (the same single fp32 add as a separate residual update, without
   // a round trip of the product through memory); with K split, their partials
   // go to `part`, as a MoE FFN's slot-order sum does, and the next residual
-  // add + RMSNorm adds them to x
+  // add + RMSNorm adds them to x.  A MoE FFN of one chunk leaves its k slots to
+  // that norm (the sum kernel's pass over them, its result written and read
+  // again: 8146 tokens at 30B-A3B widths 113 us per layer, the norm's extra 55)
   const bool moe = c.n_experts > 0;
-  int pending = 0;  // partials of the last FFN in `part`, not yet in x
+  const bool one_chunk = moe && T <= L.mc;
+  float* ffn_part = one_chunk ? reinterpret_cast<float*>(ws + L.m_slots) : part;
+  int pending = 0;  // partials of the last FFN in ffn_part, not yet in x
   for (int l = 0; l < c.n_layers; ++l) {
     {
       ProfScope ps(SEVO_PROF_NORM, st);
-      e = sevo::launch_add_rmsnorm(x, pending ? part : nullptr, pending,
+      e = sevo::launch_add_rmsnorm(x, pending ? ffn_part : nullptr, pending,
                                    static_cast<const sevo::bf16_t*>(m->attn_norm[l]), T, H,
                                    c.rms_eps, h, st);
     }
@@ -1353,9 +1358,9 @@ SEVO_API sevo_status sevo_prefill_confidence(sevo_model* m, const sevo_prefill_a
       // of the chunk, then their slot-order sum into its rows of `part`
       for (int c0 = 0; c0 < T && e == hipSuccess; c0 += L.mc) {
         const int nc = T - c0 < L.mc ? T - c0 : L.mc;
-        e = run_moe_prefill_chunk(m, l, c0, nc, h, ws, L, part, st);
+        e = run_moe_prefill_chunk(m, l, c0, nc, h, ws, L, one_chunk ? nullptr : part, st);
       }
-      pending = 1;
+      pending = one_chunk ? c.n_experts_active : 1;
     } else {
       if (e == hipSuccess) {
         ProfScope ps(SEVO_PROF_GATE_UP, st);
@@ -1378,7 +1383,7 @@ SEVO_API sevo_status sevo_prefill_confidence(sevo_model* m, const sevo_prefill_a
     const int nr = R - r0 < L.rc ? R - r0 : L.rc;
     {
       ProfScope ps(SEVO_PROF_NORM, st);
-      e = sevo::launch_add_rmsnorm(x, pending ? part : nullptr, pending,
+      e = sevo::launch_add_rmsnorm(x, pending ? ffn_part : nullptr, pending,
                                    static_cast<const sevo::bf16_t*>(m->final_norm), nr, H,
                                    c.rms_eps, hf, st, a->scored_rows + r0, T);
     }

@@ -768,6 +768,37 @@ def test_add_rmsnorm_matches_oracle_and_forms_agree(S, rows, cols, n_part):
         assert torch.equal(out.view(torch.int16), outb.view(torch.int16))
 
 
+@pytest.mark.parametrize("rows,cols,n_part", [(512, 2048, 8), (641, 4096, 5), (520, 8192, 3),
+                                                (777, 260, 16)])
+def test_add_rmsnorm_many_rows_with_many_partials(S, rows, cols, n_part):
+    """The many-row form with several partials (loaded in groups, added in
+    order; a ragged last group) and rows past the last full group of 128: bit
+    for bit the 1024-thread form's (the same rows in slices of 192)."""
+    sevo, _ = S
+    say(f"add_rmsnorm rows={rows} cols={cols} partials={n_part}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(rows + cols + n_part)
+    x0 = torch.randn(rows, cols, device="cuda", generator=g)
+    parts = torch.randn(n_part, rows, cols, device="cuda", generator=g)
+    gain = (1.0 + 0.02 * torch.randn(cols, device="cuda", generator=g)).to(torch.bfloat16)
+    xa, xb = x0.clone(), x0.clone()
+    out = sevo.sevo_add_rmsnorm(xa, parts, gain, 1e-6)
+    outb = torch.zeros_like(out)
+    for a in range(0, rows, 192):
+        b = min(rows, a + 192)
+        nb = -(-(b - a) // 16) * 16 * cols
+        sevo.sevo_add_rmsnorm(xb[a:b], parts[:, a:b].contiguous(), gain, 1e-6,
+                              out=outb[a * cols:a * cols + nb])
+    torch.cuda.synchronize()
+    assert torch.equal(xa, xb)
+    if cols % 32 == 0:   # (the tiled layout needs whole 32-column steps)
+        assert torch.equal(out.view(torch.int16), outb.view(torch.int16))
+    ref = x0.cpu().numpy()
+    for s_ in range(n_part):
+        ref = ref + parts[s_].cpu().numpy()
+    np.testing.assert_array_equal(xa.cpu().numpy(), ref)
+
+
 @pytest.mark.parametrize("hq,hkv,d", [(32, 8, 128), (64, 8, 128), (4, 2, 64)])
 def test_qk_norm_rope_append_forms_agree(S, hq, hkv, d):
     """The per-token form of QK-norm + RoPE + append (from 256 tokens) against
