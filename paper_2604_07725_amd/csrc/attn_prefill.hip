@@ -5,8 +5,8 @@
 //
 //   * one workgroup of NW waves per (sequence, NW query units, kv head); a
 //     unit is one query head of the kv head's group over 32 NQT consecutive
-//     tokens, and each wave owns one unit.  The shipped shape is 12 waves of
-//     32 queries: 162 registers per wave, so three waves share each SIMD and
+//     tokens, and each wave owns one unit.  The shape of a large call is 12 waves
+//     of 32 queries: 162 registers per wave, so three waves share each SIMD and
 //     the MFMAs of one overlap the softmax of the others (8 waves, two per
 //     SIMD, measured 5% slower; 16 waves spill; 4 waves of 64 queries, one per
 //     SIMD, 16% slower than 8, and a hand-pipelined single wave spilled);
@@ -23,7 +23,8 @@
 //     loads through a per-page buffer descriptor (waves 0-7, two per page: one
 //     K tile, one V tile) -- a page id outside the pool, or a page past the
 //     workgroup's keys, gets zero records and reads zeros; four LDS stages
-//     hold the block being multiplied and up to three more in flight;
+//     hold the block being multiplied and up to three more in flight (small
+//     calls: four waves and two stages, see kPfFewGroups);
 //   * the keys of a page whose id lies outside the pool are left out, as in
 //     decode.  Such ids are a caller's error, so the hot loop stays as it is
 //     unless the workgroup finds one among its pages in a pre-pass; then each
@@ -53,9 +54,6 @@ namespace sevo {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-constexpr int kPfStages = 4;
-constexpr int kPfWaves = 12;     // waves per workgroup
-constexpr int kPfQueryTiles = 1; // 32-query tiles per wave
 // Score given to a key on a page outside the pool.  Far below any real score
 // (|q . k| of ordinary bf16 inputs is many orders smaller), yet small enough
 // that its product with the scale, rounded to fp32, is off by well under 1 in
@@ -70,12 +68,15 @@ constexpr float kAbsentKey = -1e6f;
 __device__ __forceinline__ int pf_kswz(int s) { return ((s >> 1) ^ (s >> 2)) & 3; }
 __device__ __forceinline__ int pf_vswz(int e) { return ((e >> 2) ^ (e >> 3)) & 1; }
 
-template <int D, int NW, int NQT>
-__global__ __launch_bounds__(64 * NW, 1) void attn_prefill_kernel(PrefillAttnArgs a) {
+// NW waves (units) per workgroup, NS LDS stages
+template <int D, int NW, int NS>
+__global__ __launch_bounds__(64 * NW, (NW == 4 ? 2 : 1)) void attn_prefill_kernel(PrefillAttnArgs a) {
+  constexpr int NQT = 1;  // 32-query tiles per wave
+  constexpr int AHEAD = NS < 3 ? NS : 3;  // blocks issued up to the one multiplied next
   constexpr int KT_ELEMS = 16 * D, PAGE_ELEMS = 2 * KT_ELEMS, STAGE_ELEMS = 4 * PAGE_ELEMS;
   constexpr int KB = D / 32, KS = D / 16, UQ = 32 * NQT;
   constexpr int DMA = NW == 4 ? 2 * KB : KB;
-  __shared__ __attribute__((aligned(1024))) bf16_t smem[kPfStages * STAGE_ELEMS];
+  __shared__ __attribute__((aligned(1024))) bf16_t smem[NS * STAGE_ELEMS];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // the kv head is the fastest-varying part of the launch order, so the
@@ -116,7 +117,7 @@ __global__ __launch_bounds__(64 * NW, 1) void attn_prefill_kernel(PrefillAttnArg
     any_absent |= pg < 0 || (int64_t)pg >= a.num_pages;
   }
   any_absent = __syncthreads_or(any_absent);
-  uint32_t absent = 0;  // bit 4 (b % kPfStages) + j: page j of that stage's block is absent
+  uint32_t absent = 0;  // bit 4 (b % NS) + j: page j of that stage's block is absent
   // the sequence's page ids through the constant address space: the kernel
   // never writes the table, and wave-uniform reads then become scalar loads
   // (a vector load here would make the compiler wait for every outstanding
@@ -135,14 +136,14 @@ __global__ __launch_bounds__(64 * NW, 1) void attn_prefill_kernel(PrefillAttnArg
         const int pg = pj < a.max_pages ? ptab[pj] : -1;
         if (pg < 0 || (int64_t)pg >= a.num_pages) bad |= 1u << j;
       }
-      const int sh = 4 * (b % kPfStages);
+      const int sh = 4 * (b % NS);
       absent = (absent & ~(0xFu << sh)) | (bad << sh);
     }
     const bool ok = page >= 0 && (int64_t)page < a.num_pages;
     const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<bf16_t*>(a.kv_pool + (ok ? ((size_t)page * a.hkv + c) * PAGE_ELEMS : 0)), 0,
         ok ? PAGE_ELEMS * 2 : 0, 0x00020000);
-    bf16_t* dst = smem + (b % kPfStages) * STAGE_ELEMS + (NW == 4 ? wave : wave >> 1) * PAGE_ELEMS;
+    bf16_t* dst = smem + (b % NS) * STAGE_ELEMS + (NW == 4 ? wave : wave >> 1) * PAGE_ELEMS;
     if (NW > 8 && wave >= 8) return;  // waves 8.. load nothing
     if (NW == 4 || (wave & 1) == 0) {
 #pragma unroll
@@ -183,9 +184,9 @@ __global__ __launch_bounds__(64 * NW, 1) void attn_prefill_kernel(PrefillAttnArg
   for (int qt = 0; qt < NQT; ++qt) { m_run[qt] = -INFINITY; l_run[qt] = 0.f; }
   const float sl2 = a.scale * 1.4426950408889634f;
 
-  for (int st = 0; st < 3 && st < nkb; ++st) issue(st);
-  if (nkb >= 3) wait_vmcnt<2 * DMA>();
-  else if (nkb == 2) wait_vmcnt<DMA>();
+  for (int st = 0; st < AHEAD && st < nkb; ++st) issue(st);
+  if (AHEAD == 3 && nkb >= 3) wait_vmcnt<2 * DMA>();
+  else if (nkb >= 2) wait_vmcnt<DMA>();
   else wait_vmcnt<0>();
   lds_barrier();
   const int nkeys = p0 + L;  // the sequence's keys; later slots may hold anything
@@ -200,7 +201,7 @@ __global__ __launch_bounds__(64 * NW, 1) void attn_prefill_kernel(PrefillAttnArg
       // the block with the sequence's last key: its V slots past that key
       // are zeroed in LDS (P is 0 there, but 0 x NaN would not be); uniform
       // over the workgroup
-      bf16_t* so = smem + (b % kPfStages) * STAGE_ELEMS + KT_ELEMS;
+      bf16_t* so = smem + (b % NS) * STAGE_ELEMS + KT_ELEMS;
       for (int idx = threadIdx.x; idx < 4 * D; idx += 64 * NW) {
         const int j = idx / D, e = idx - (idx / D) * D;
         for (int sl = 0; sl < kPage; ++sl)
@@ -210,7 +211,7 @@ __global__ __launch_bounds__(64 * NW, 1) void attn_prefill_kernel(PrefillAttnArg
       lds_barrier();
     }
     if (active && b <= last_b) {
-      const bf16_t* so = smem + (b % kPfStages) * STAGE_ELEMS;
+      const bf16_t* so = smem + (b % NS) * STAGE_ELEMS;
       f32x16 acc_s[2][NQT];
 #pragma unroll
       for (int kt = 0; kt < 2; ++kt)
@@ -240,7 +241,7 @@ __global__ __launch_bounds__(64 * NW, 1) void attn_prefill_kernel(PrefillAttnArg
               if (key > qpos[qt]) acc_s[kt][qt][e] = -INFINITY;
             }
         }
-        const uint32_t bad = any_absent ? (absent >> (4 * (b % kPfStages))) & 0xFu : 0u;
+        const uint32_t bad = any_absent ? (absent >> (4 * (b % NS))) & 0xFu : 0u;
         if (bad) {
           // element e of tile kt holds a key of page 2 kt + e / 8 of the block
 #pragma unroll
@@ -299,11 +300,12 @@ __global__ __launch_bounds__(64 * NW, 1) void attn_prefill_kernel(PrefillAttnArg
         }
     }
     if (b + 1 < nkb) {
-      if (b + 2 < nkb) wait_vmcnt<DMA>();
+      // block b + 1 has landed; b + 2 may still be loading
+      if (AHEAD == 3 && b + 2 < nkb) wait_vmcnt<DMA>();
       else wait_vmcnt<0>();
       wait_lgkm0();
-      lds_barrier();
-      if (b + 3 < nkb) issue(b + 3);
+      lds_barrier();  // every wave is done with block b, whose buffer is free
+      if (b + AHEAD < nkb) issue(b + AHEAD);
     }
   }
   wait_vmcnt<0>();
@@ -328,17 +330,30 @@ __global__ __launch_bounds__(64 * NW, 1) void attn_prefill_kernel(PrefillAttnArg
       }
   }
 }
-hipError_t launch_attn_prefill(const PrefillAttnArgs& a, hipStream_t st) {
-  if (a.n_seqs == 0 || a.max_seq_len <= 0) return hipSuccess;
-  constexpr int NW = kPfWaves, NQT = kPfQueryTiles;
-  const int g = a.hq / a.hkv;
-  const int units = ((a.max_seq_len + 32 * NQT - 1) / (32 * NQT)) * g;
+// Twelve-wave groups (one per CU) while there are enough of them; a call of at
+// most this many takes workgroups of four waves and two stages, two per CU:
+// three times the groups, a third of the chain of its longest one (us, 12 / 4
+// waves, 32/8 heads: 1000 tokens 44 / 29, 2000 81 / 55, 4000 163 / 152, 6000 291
+// / 304; 300 tokens behind 4000 cached ones at 32/4 heads 113 / 66; 4/2 heads of
+// 64, 16000 tokens 401 / 234).
+constexpr double kPfFewGroups = 400.0;
+
+template <int NW, int NS>
+static hipError_t launch_prefill_t(const PrefillAttnArgs& a, hipStream_t st) {
+  const int units = ((a.max_seq_len + 31) / 32) * (a.hq / a.hkv);
   const dim3 grid((units + NW - 1) / NW, a.hkv, a.n_seqs);
   if (a.d == 128)
-    hipLaunchKernelGGL((attn_prefill_kernel<128, NW, NQT>), grid, dim3(64 * NW), 0, st, a);
+    hipLaunchKernelGGL((attn_prefill_kernel<128, NW, NS>), grid, dim3(64 * NW), 0, st, a);
   else
-    hipLaunchKernelGGL((attn_prefill_kernel<64, NW, NQT>), grid, dim3(64 * NW), 0, st, a);
+    hipLaunchKernelGGL((attn_prefill_kernel<64, NW, NS>), grid, dim3(64 * NW), 0, st, a);
   return hipGetLastError();
+}
+
+hipError_t launch_attn_prefill(const PrefillAttnArgs& a, hipStream_t st) {
+  if (a.n_seqs == 0 || a.max_seq_len <= 0) return hipSuccess;
+  const double units = ((double)a.total_tokens / 32 + a.n_seqs) * (a.hq / a.hkv);
+  if (units * a.hkv / 12 <= kPfFewGroups) return launch_prefill_t<4, 2>(a, st);
+  return launch_prefill_t<12, 4>(a, st);
 }
 
 }  // namespace sevo

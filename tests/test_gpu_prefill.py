@@ -416,6 +416,38 @@ def test_attn_prefill_absent_pages_contribute_no_keys(S, dims):
     assert worst <= min(ATTN_REL_TOL, 8e-3)
 
 
+@pytest.mark.parametrize("dims", [(64, 8, 128), (64, 8, 64)])
+def test_attn_prefill_small_and_large_calls_agree(S, dims):
+    """The twelve-wave form (a batch of many query groups) and the four-wave one
+    (each sequence alone) give the same bits: ragged lengths, cached prefixes,
+    NaN in the slots past the last key and, in the last sequence, an absent
+    page."""
+    sevo, di = S
+    hq, hkv, d = dims
+    say(f"attn prefill forms {dims}")
+    lens, starts = np.array([1501, 700, 2317, 64]), np.array([0, 133, 0, 200])
+    pop = make_population(starts + lens, shuffle=True, seed=9)
+    kvp = di.device_pools(_shape(*dims), 9, pop.n_pages, layers=[0])[0]
+    for i, n in enumerate(starts + lens):          # V slots past each last key
+        if n % 16:
+            tile = kvp[int(pop.page_table[i, n // 16]), :, 1].view(hkv, d, 16)
+            tile[:, :, n % 16:] = float("nan")
+    pt = torch.from_numpy(pop.page_table.astype(np.int32)).cuda()
+    pt[3, 2] = pop.n_pages + 5
+    ss = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    q = di.device_q(_shape(*dims), 9, int(lens.sum()))
+    sp = torch.from_numpy(starts.astype(np.int32)).cuda()
+    out = sevo.sevo_attn_prefill(q, kvp, pt, torch.from_numpy(ss).cuda(), int(lens.max()),
+                                 start_pos=sp)
+    for i, n in enumerate(lens):
+        one = sevo.sevo_attn_prefill(q[ss[i]:ss[i + 1]], kvp, pt[i:i + 1].clone(),
+                                     torch.tensor([0, n], dtype=torch.int32, device="cuda"), int(n),
+                                     start_pos=sp[i:i + 1].clone())
+        torch.cuda.synchronize()
+        assert torch.isfinite(one.float()).all()
+        assert torch.equal(out[ss[i]:ss[i + 1]].view(torch.int16), one.view(torch.int16))
+
+
 @pytest.mark.parametrize("workload", ["tiny_step", "tiny_moe_step"])
 def test_prefill_confidence_without_room_for_split_partials(S, workload):
     """A workspace without room for the projections' split partials is accepted
