@@ -52,8 +52,6 @@ namespace sevo {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-constexpr int kLgStages = 4;  // LDS stages: one multiplied, up to three loading
-
 // One direct load of a wave per stage: a 1 KB operand fragment (16 rows x 32
 // columns) through a wave-uniform descriptor over the region it streams.
 struct LgLoad {
@@ -76,10 +74,11 @@ __device__ __forceinline__ void lg_groups(F f) {
 // XT 1: X in the tiled activation layout, else row-major with stride ldx
 // GR 1: grouped (M = the rows of X: tokens for gate/up, entries for down)
 // Tile BM x BN, NW waves in a grid of NW / (BN / 64) x BN / 64; a stage is
-// KSUB 32-column steps.  Split K (EPI 0): blockIdx.y takes kchunk columns and
+// KSUB 32-column steps.  NS LDS stages, one multiplied and up to NS - 1 loading
+// (three: two workgroups per CU).  Split K (EPI 0): blockIdx.y takes kchunk columns and
 // writes the partial out[blockIdx.y][M][ldo].
-template <int BM, int BN, int NW, int KSUB, int EPI, int XT, int GR>
-__global__ __launch_bounds__(64 * NW, 1) void
+template <int BM, int BN, int NW, int KSUB, int EPI, int XT, int GR, int NS = 4>
+__global__ __launch_bounds__(64 * NW, (NS == 3 ? 4 : 1)) void
 gemm_large_kernel(const bf16_t* __restrict__ X, int ldx, int M, const bf16_t* __restrict__ W,
                   int N, int K, int kchunk, float* __restrict__ out, int ldo,
                   bf16_t* __restrict__ out_bf16, int out_tiled, int tiles_m, int tiles_n,
@@ -92,7 +91,7 @@ gemm_large_kernel(const bf16_t* __restrict__ X, int ldx, int M, const bf16_t* __
   constexpr int D = (KSUB * FS + NW - 1) / NW;    // direct loads per wave and stage
   constexpr bool kIdle = D * NW != KSUB * FS;     // some waves have one load too many
   constexpr int STAGE = KSUB * SUB + (kIdle ? NW * 512 : 0);
-  __shared__ __attribute__((aligned(1024))) bf16_t smem[kLgStages * STAGE];
+  __shared__ __attribute__((aligned(1024))) bf16_t smem[NS * STAGE];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / WN, wn = wave % WN;
@@ -100,7 +99,7 @@ gemm_large_kernel(const bf16_t* __restrict__ X, int ldx, int M, const bf16_t* __
   // ---- tile order: XCD-contiguous ranges, groups of GM m-tiles.  Grouped: of
   // the tiles that the entry lists fill (the grid has room for a part-filled
   // tile per expert more; dividing that among the XCDs left the last ones idle)
-  if constexpr (GR) tiles_m = g.tile_off[g.E];
+  if constexpr (GR) tiles_m = g.tile_off[g.E] * g.sub;
   const int total = tiles_m * tiles_n;
   int t = blockIdx.x;
   if (GR && t >= total) return;  // uniform over the workgroup, before any barrier
@@ -121,15 +120,17 @@ gemm_large_kernel(const bf16_t* __restrict__ X, int ldx, int M, const bf16_t* __
   int rows = M;      // rows of this tile's matrix (the expert's entries)
   int ent0 = 0;      // first entry of the expert
   if constexpr (GR) {
-    int lo = 0, hi = g.E;  // tile_off[lo] <= tm < tile_off[hi]
+    const int table_tile = tm / g.sub, part = tm - table_tile * g.sub;
+    int lo = 0, hi = g.E;  // tile_off[lo] <= table_tile < tile_off[hi]
     while (hi - lo > 1) {
       const int mid = (lo + hi) >> 1;
-      if (g.tile_off[mid] <= tm) lo = mid;
+      if (g.tile_off[mid] <= table_tile) lo = mid;
       else hi = mid;
     }
     ent0 = g.offsets[lo];
     rows = g.offsets[lo + 1] - ent0;
-    m0 = (tm - g.tile_off[lo]) * BM;
+    m0 = ((table_tile - g.tile_off[lo]) * g.sub + part) * BM;
+    if (m0 >= rows) return;  // uniform, before any barrier
     W += (size_t)lo * N * K;
   }
 
@@ -199,7 +200,7 @@ gemm_large_kernel(const bf16_t* __restrict__ X, int ldx, int M, const bf16_t* __
   }
   // loads [i0, i1) of stage st
   auto issue = [&](int st, int i0, int i1) {
-    bf16_t* so = smem + (st & (kLgStages - 1)) * STAGE;
+    bf16_t* so = smem + (st % NS) * STAGE;
 #pragma unroll
     for (int i = 0; i < D; ++i)
       if (i >= i0 && i < i1) dma16(ld[i].r, ld[i].voff + (ld[i].soff + st * ld[i].step), so + ld[i].lds);
@@ -230,7 +231,7 @@ gemm_large_kernel(const bf16_t* __restrict__ X, int ldx, int M, const bf16_t* __
   };
   // operand runs of 16-k group h of stage st
   auto read = [&](Frags& f, int st, int h) {
-    const bf16_t* so = smem + (st & (kLgStages - 1)) * STAGE + (h >> 1) * SUB + (h & 1) * 256;
+    const bf16_t* so = smem + (st % NS) * STAGE + (h >> 1) * SUB + (h & 1) * 256;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
       f.a[mt] = *reinterpret_cast<const bf16x8v*>(so + a_off + mt * 1024);
@@ -249,9 +250,9 @@ gemm_large_kernel(const bf16_t* __restrict__ X, int ldx, int M, const bf16_t* __
                          : __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[mt], f.b[nt], acc[mt][nt], 0, 0, 0);
   };
 
-  // Pipeline: up to three stages of direct loads are in flight while one is
+  // Pipeline: up to NS - 1 stages of direct loads are in flight while one is
   // multiplied.  Group h of stage kt: the LDS reads of the next group and a
-  // share of stage kt + 3's direct loads (its buffer held stage kt - 1, which
+  // share of stage kt + NS - 1's direct loads (its buffer held stage kt - 1, which
   // every wave finished reading before the last barrier) are interleaved with
   // the group's MFMAs; before the last group, whose reads are of stage kt + 1,
   // that stage is waited for and the waves meet.  sched_group_barrier masks:
@@ -270,8 +271,8 @@ gemm_large_kernel(const bf16_t* __restrict__ X, int ldx, int M, const bf16_t* __
     }
   };
   Frags fr[2];
-  for (int st = 0; st < 3; ++st) issue(st, 0, D);
-  wait_vmcnt<2 * D>();  // stage 0 landed
+  for (int st = 0; st < NS - 1; ++st) issue(st, 0, D);
+  wait_vmcnt<(NS - 2) * D>();  // stage 0 landed
   lds_barrier();
   read(fr[0], 0, 0);
   for (int kt = 0; kt < nst; ++kt) {
@@ -279,14 +280,14 @@ gemm_large_kernel(const bf16_t* __restrict__ X, int ldx, int M, const bf16_t* __
       constexpr int h = decltype(h_tag)::value;
       constexpr int i0 = D * h / H, i1 = D * (h + 1) / H;
       if constexpr (h == H - 1) {
-        // stage kt + 2 and this stage's share of kt + 3 may still be loading
+        // the stages from kt + 2 on and this stage's share of the last may still be loading
         // (after the last stage this reads a stale buffer that is never used:
         // keeping the step unconditional keeps the LDS reads interleaved)
-        wait_vmcnt<D + i0>();
+        wait_vmcnt<(NS - 3) * D + i0>();
         wait_lgkm0();
         lds_barrier();
       }
-      issue(kt + 3, i0, i1);
+      issue(kt + NS - 1, i0, i1);
       if constexpr (h == H - 1) read(fr[(h + 1) & 1], kt + 1, 0);
       else read(fr[(h + 1) & 1], kt, h + 1);
       mma(fr[h & 1]);
@@ -408,10 +409,10 @@ struct LgArgs {
   hipStream_t st;
 };
 
-template <int BM, int BN, int NW, int KSUB, int EPI, int XT, int GR>
+template <int BM, int BN, int NW, int KSUB, int EPI, int XT, int GR, int NS = 4>
 hipError_t run_lg(const LgArgs& a, int tiles_m, const GroupArgs& g) {
   const int tiles_n = (a.n_out + BN - 1) / BN;
-  hipLaunchKernelGGL((gemm_large_kernel<BM, BN, NW, KSUB, EPI, XT, GR>),
+  hipLaunchKernelGGL((gemm_large_kernel<BM, BN, NW, KSUB, EPI, XT, GR, NS>),
                      dim3(tiles_m * tiles_n, a.splits), dim3(64 * NW), 0, a.st, a.x, a.ldx, a.m, a.w,
                      a.n_out, a.k, a.kchunk, static_cast<float*>(a.out), a.n_out,
                      static_cast<bf16_t*>(a.out), a.out_tiled, tiles_m, tiles_n, g);
@@ -513,11 +514,26 @@ int moe_group_rows(long long entries, int n_experts) {
   return entries < 96ll * n_experts ? 128 : 256;
 }
 
+// The down projection of 256-entry tiles in halves of 128, two workgroups per CU
+// (three LDS stages of 24 KB, 99 registers): a short K leaves it bound by its
+// scattered fp32 stores, which then run under the other workgroup's products,
+// and an expert's last tile pads to 128 entries.  Scoring at 30B-A3B widths, two
+// layers, us with whole tiles / halves: 509 entries per expert 3558 / 3510, 250
+// each 1981 / 1957, 1250 each 9460 / 9403; 125 each 1238 / 1282, so the line lies
+// between.  With the gate/up product on such tiles too 509 each took 3537 against
+// 3469, and below 96 entries, on 128-entry tiles, 62 each 980 against 969.
+constexpr long long kHalvedMinEntries = 192;
+
 hipError_t launch_gemm_grouped(int down, int m, int n_out, int k, const bf16_t* x,
                                const bf16_t* w, void* out, const GroupArgs& g, int tile_rows,
                                int max_tiles_m, hipStream_t st) {
   if (m == 0 || max_tiles_m == 0) return hipSuccess;
   const LgArgs a{m, n_out, k, k, 1, k, x, w, out, 0, st};
+  if (tile_rows == 256 && down && (long long)m >= kHalvedMinEntries * g.E) {
+    GroupArgs half = g;
+    half.sub = 2;
+    return run_lg<128, 256, 8, 1, 3, 0, 1, 3>(a, 2 * max_tiles_m, half);
+  }
   if (tile_rows == 128)
     return down ? run_lg<128, 256, 8, 1, 3, 0, 1>(a, max_tiles_m, g)
                 : run_lg<128, 256, 8, 1, 2, 0, 1>(a, max_tiles_m, g);

@@ -166,6 +166,7 @@ struct GroupArgs {
   const int32_t* tile_off = nullptr;  // [E + 1] first tile of each expert
   const float* weights = nullptr;     // [n k] routing weights (down)
   int E = 0, k = 1, n = 0;            // experts, top-k, tokens
+  int sub = 1;                        // workgroup tiles per tile of tile_off
 };
 // down 0: gate/up of every entry, x = the row-major normed input (m = tokens),
 //   out bf16 act [n k][n_out / 2] at the entry positions (SwiGLU);

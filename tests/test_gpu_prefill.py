@@ -346,6 +346,25 @@ def test_prefill_confidence_tiny_moe_matches_oracle(S, lens, moe_chunk):
     assert np.abs(g_conf - conf).max() <= 1e-2
 
 
+def test_prefill_confidence_tiny_moe_halved_down_tiles(S):
+    """3200 tokens of the tiny MoE, 200 entries per expert on average: the down
+    projection runs its 256-entry tiles in halves of 128, the lists ending in
+    part-filled and empty halves.  Bars of the other tiny MoE cases; this seed
+    has no routing choice closer than 1e-5."""
+    shape, seed, lens = synth.TINY_MOE, 14, [1700, 1500]
+    scored = list(range(40, 1700, 3)) + list(range(1720, 3200, 3))
+    say("prefill confidence (tiny MoE, halved down tiles)")
+    (g_conf, g_row, _), pop, toks, seq_starts, _ = _engine_case(S, shape, seed, lens, scored, 20)
+    hw = synth.host_weights(shape, seed)
+    hkv = [p.astype(np.float64) for p in synth.host_pools(shape, seed, pop.n_pages)]
+    stats = {}
+    conf, c, _ = od.prefill_confidence(shape, hw, hkv, pop.page_table, toks, seq_starts, scored,
+                                       20, stats=stats)
+    assert stats["route_gap"] > 1e-5, "test input has a routing near-tie"
+    assert np.abs(g_row - c).max() <= 2e-2
+    assert np.abs(g_conf - conf).max() <= 1e-2
+
+
 @pytest.mark.parametrize("moe_chunk", [0, 256])
 def test_prefill_confidence_moe30b_reduced_depth(S, moe_chunk):
     """The 30B-A3B-class MoE widths (hidden 2048, 32/4 heads, 128 experts of
