@@ -494,8 +494,9 @@ sevo_status sevo_add_rmsnorm(float* x, const float* partials, int32_t n_partials
  *                                else row-major with row stride ldx, ldx % 8 == 0)
  *        SEVO_LINEAR_OUT_TILED   SWIGLU output in the tiled activation layout
  * k % 32 == 0; n_out % 64 == 0.  k_splits 0 = chosen by the library (SWIGLU
- * always uses one split; from m = 256 on the library always chooses, and a
- * workspace below sevo_linear_workspace_bytes, or none, means one split). */
+ * always uses one split; k_splits 1 is kept at every m, another count below m =
+ * 256, where the library chooses from then on; there a workspace below
+ * sevo_linear_workspace_bytes, or none, means one split). */
 #define SEVO_LINEAR_STORE 0
 #define SEVO_LINEAR_ADD 1
 #define SEVO_LINEAR_SWIGLU 2

@@ -155,7 +155,9 @@ hipError_t launch_linear_partials(int m, int n_out, int k, int ldx, int x_tiled,
 // operand layouts and epilogue modes as launch_linear; with K split, mode 0
 // writes the partials [split][m][n].  fixed_splits 0: chosen, at most max_splits
 constexpr int kTileMinM = 65;
-// from here on a caller's k_splits is not taken and no workspace is required
+// from here on a caller's k_splits other than 1 is not taken and no workspace is
+// required.  One split is binding at every m: its caller has room for the product
+// alone (the LM head writes it over the logits)
 constexpr int kLargeGemmMinM = 256;
 LinearPlan plan_tiles(int m, int n_out, int k, int mode, int fixed_splits, int max_splits);
 // grouped form (mixture of experts): m-tiles are tiles of tile_rows entries of

@@ -293,7 +293,8 @@ LinearPlan plan_linear(int m, int n_out, int k, int k_splits, int mode, int max_
   // at m = 128: 43 us, tiles 49)
   if (m >= kTileMinM && max_mb > kLinearSmallMb &&
       !(mode == 2 && m <= 128 && n_out < 192 * 256))
-    return plan_tiles(m, n_out, k, mode, m < kLargeGemmMinM ? k_splits : 0, max_splits);
+    return plan_tiles(m, n_out, k, mode, m < kLargeGemmMinM || k_splits == 1 ? k_splits : 0,
+                      max_splits);
   const int mb = pick_mb(m, n_out, k, max_mb);
   const int mt = (m + 16 * mb - 1) / (16 * mb);
   const int swiglu = mode == 2;
@@ -434,6 +435,7 @@ hipError_t launch_linear_partials(int m, int n_out, int k, int ldx, int x_tiled,
                                   const LinearPlan& plan, const bf16_t* x, const bf16_t* w,
                                   float* out, int accumulate, hipStream_t st) {
   if (m == 0) return hipSuccess;
+  if (accumulate && plan.k_splits != 1) return hipErrorInvalidValue;  // partials are stored
   if (plan.tile)
     return launch_gemm_large(m, n_out, k, ldx, x_tiled, accumulate ? 1 : 0, plan, x, w, out, 0, st);
   const LinearLaunch a{linear_grid(m, n_out, 0, plan), st, x, ldx, m, w, n_out, k, plan.k_chunk,

@@ -764,7 +764,8 @@ StepLayout step_layout(const sevo_model_config& c, int n, int max_pages, int num
     L.p_gu = L.p_d = sevo::LinearPlan{1, c.hidden};
     L.p_router = sevo::plan_linear(n, c.n_experts, c.hidden, 0, SEVO_LINEAR_STORE, max_mb);
   }
-  L.p_lm = sevo::plan_linear(n, c.vocab, c.hidden, 1, SEVO_LINEAR_STORE, max_mb);
+  // one split: L.logits (and out_logits) holds the product, no partials
+  L.p_lm = sevo::plan_linear(n, c.vocab, c.hidden, 1, SEVO_LINEAR_STORE, max_mb, 1);
   size_t off = 0;
   auto take = [&](size_t bytes) {
     const size_t o = off;

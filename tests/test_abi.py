@@ -202,6 +202,17 @@ def test_linear_plans_of_the_decode_projections():
     assert plan(64, 6144, 4096, k_splits=3)[0] == 3
 
 
+@pytest.mark.parametrize("n", [1, 64, 65, 128, 255, 256, 257, 300, 512, 1000, 4096])
+def test_one_split_is_binding_at_every_m(n):
+    """A caller that asks for one split has room for the product alone: no
+    workspace is asked for, whatever the vocabulary and width of an LM head
+    (4096 x 4096 at 256 rows would otherwise run in 4 splits)."""
+    L = sevo.lib()
+    for vocab in (64, 256, 1024, 4096, 8192, 16384, 32000, 151936):
+        for hidden in (128, 256, 1024, 2048, 4096, 5120):
+            assert L.sevo_linear_workspace_bytes(n, vocab, hidden, 1) == 0, (vocab, hidden)
+
+
 @pytest.mark.parametrize("args", [(0, 128, 256, 0, 0), (256, 128, 256, 0, 0), (4, 96, 256, 0, 0),
                                   (4, 128, 48, 0, 0), (4, 128, 256, -1, 0), (4, 128, 256, 0, 3)])
 def test_linear_plan_rejects_bad_shapes(args):

@@ -234,6 +234,55 @@ def test_full_width_step_reduced_depth(S, workload, layers):
             assert z.max() - z[g_ids[j]] <= FULL_GAP_EXACT
 
 
+@pytest.mark.parametrize("n", [256, 300])
+def test_step_of_many_candidates_with_a_small_vocabulary(S, n):
+    """From 256 rows on the projections run in K splits where that fills the
+    chip, and a 4096 x 2048 LM head would too: it has room for the product
+    alone.  Logits, ids and log-probs of sampled candidates against the oracle,
+    nothing written behind out_logits, and the same step with the logits kept in
+    the workspace."""
+    import ctypes as C
+    sevo, di = S
+    shape = synth.ModelShape(n_layers=1, hidden=2048, n_q_heads=16, n_kv_heads=4, head_dim=128,
+                             ffn=512, vocab=4096)
+    seed, temp = 41, 1.0
+    say(f"step of {n} candidates, vocabulary 4096")
+    lens = 20 + np.arange(n) % 37
+    pop = synth.make_population(n, lens, shape.vocab, seed, 1, True)
+    model = sevo.sevo_init_model(shape, di.device_weights(shape, seed), max_position=64)
+    d = di.device_population(pop)
+    guard = 3 * n * shape.vocab            # what three more partials would cover
+    big = torch.full((n * shape.vocab + guard,), 7.0, dtype=torch.float32, device="cuda")
+    ws = poisoned(sevo.sevo_step_workspace_bytes(model, n, pop.max_pages))
+    out = []
+    for logits_ptr in (big.data_ptr(), None):
+        kvp = di.device_pools(shape, seed, pop.n_pages)
+        b = sevo.StepBuffers(model, d["tokens"], d["lengths"], d["page_table"], kvp, d["uids"],
+                             seed, temp, workspace=ws, conf_topk=20)
+        b.args.out_logits = C.c_void_p(logits_ptr)
+        ids, lps = b.run()
+        torch.cuda.synchronize()
+        out.append([t.cpu().numpy() for t in (ids, lps, b.out_conf)])
+    assert bool((big[n * shape.vocab:] == 7.0).all()), "written behind out_logits"
+    for a, b in zip(*out):
+        np.testing.assert_array_equal(a, b)
+    ids, lps, conf = out[0]
+    idx = [0, 1, 127, 128, 255, n - 1]
+    g = big[:n * shape.vocab].view(n, -1).double().cpu().numpy()[idx]
+    hkv, hpt = subset_host_state(shape, seed, pop, idx, 1)
+    ref = od.decode_step(shape, synth.host_weights(shape, seed), hkv, hpt, pop.tokens[idx],
+                         pop.lengths[idx], pop.uids[idx], seed, temp)
+    err = np.abs(g - ref["logits"]).max()
+    say(f"  logit max abs err {err:.2e} (max |logit| {np.abs(ref['logits']).max():.2f})")
+    assert err <= FULL_LOGIT_TOL
+    assert np.abs(conf[idx] - od.token_confidence(ref["logits"], 20)).max() <= 2 * FULL_LOGIT_TOL
+    assert np.abs(lps[idx] - ref["lps"])[ids[idx] == ref["ids"]].max() <= FULL_LP_TOL
+    for j, i in enumerate(idx):
+        if ref["gaps"][j] > FULL_GAP_EXACT:
+            assert ids[i] == ref["ids"][j]
+    model.close()
+
+
 def test_step_graph_replay_matches_eager_bit_exact(S):
     """The decode step captured as a HIP graph (launches of sevo_decode_step and
     the on-device bookkeeping) replays bit-identically to eager steps on a copy
