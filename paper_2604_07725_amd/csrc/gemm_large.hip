@@ -142,8 +142,10 @@ gemm_large_kernel(const bf16_t* __restrict__ X, int ldx, int M, const bf16_t* __
   const int last_sb = (N >> 6) - 1;
 
   // ---- this wave's direct loads: fragments wave, wave + NW, ... of a stage.
-  // The descriptors end with the split, so the stages past the last one (the
-  // loop issues full stages throughout) load zeros and touch no memory.
+  // The loop issues full stages throughout.  The descriptors of W and of a tiled
+  // X end with the split, so the stages past the last one load zeros from them
+  // and touch no memory; of a row-major X they may read later columns of the
+  // rows before the last.  Those stages are not multiplied.
   LgLoad ld[D];
 #pragma unroll
   for (int i = 0; i < D; ++i) {
@@ -179,10 +181,12 @@ gemm_large_kernel(const bf16_t* __restrict__ X, int ldx, int M, const bf16_t* __
           l.step = KSUB * 1024u;
         } else {
           // run p = lane of the fragment is row 16 blk + p % 16, columns
-          // 8 (p / 16) .. + 8 of the step; rows past M fall outside the records
+          // 8 (p / 16) .. + 8 of the step; rows past M fall outside the records,
+          // which end with the last row's columns of the split (X may be a
+          // column slice that ends there)
           const int nr = min(16, M - 16 * blk);
           l.r = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(X + (size_t)16 * blk * ldx), 0,
-                                                  nr * ldx * 2, 0x00020000);
+                                                  ((nr - 1) * ldx + ks1 * 32) * 2, 0x00020000);
           l.voff = ((lane & 15) * ldx + 8 * (lane >> 4)) * 2;
           l.soff = (ks0 + sub) * 64u;
           l.step = KSUB * 64u;

@@ -155,6 +155,10 @@ hipError_t launch_linear_partials(int m, int n_out, int k, int ldx, int x_tiled,
 // operand layouts and epilogue modes as launch_linear; with K split, mode 0
 // writes the partials [split][m][n].  fixed_splits 0: chosen, at most max_splits
 constexpr int kTileMinM = 65;
+// the tiles' byte offsets inside a 64-row weight superblock (128 k) and a 16-row
+// block of a row-major X (32 ldx) are 32-bit; longer rows stay with the skinny
+// kernel, whose addresses are 64-bit
+constexpr int kTileMaxK = (1 << 24) - 1, kTileMaxLdx = 1 << 26;
 // from here on a caller's k_splits other than 1 is not taken and no workspace is
 // required.  One split is binding at every m: its caller has room for the product
 // alone (the LM head writes it over the logits)

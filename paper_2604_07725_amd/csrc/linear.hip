@@ -291,7 +291,7 @@ LinearPlan plan_linear(int m, int n_out, int k, int k_splits, int mode, int max_
   // QKV 26 -> 22, output 21 -> 16).  A gate/up matrix cannot split K: up to 128
   // rows, one too narrow for 192 tiles of 256 columns stays here (24576 x 4096
   // at m = 128: 43 us, tiles 49)
-  if (m >= kTileMinM && max_mb > kLinearSmallMb &&
+  if (m >= kTileMinM && max_mb > kLinearSmallMb && k <= kTileMaxK &&
       !(mode == 2 && m <= 128 && n_out < 192 * 256))
     return plan_tiles(m, n_out, k, mode, m < kLargeGemmMinM || k_splits == 1 ? k_splits : 0,
                       max_splits);

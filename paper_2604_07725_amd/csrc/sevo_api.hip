@@ -630,14 +630,22 @@ SEVO_API sevo_status sevo_linear(const sevo_linear_args* a, void* stream) {
   if (a->m == 0) return SEVO_OK;
   if (!a->x || !a->w || !a->out || !aligned16(a->x) || !aligned16(a->w) || !aligned16(a->out))
     return fail(SEVO_ERR_INVALID_ARGUMENT, "null or misaligned pointer");
-  sevo::LinearPlan plan = sevo::plan_linear(a->m, a->n_out, a->k, a->k_splits, a->mode);
+  // rows too far apart for the tiles: the skinny kernel, in one split unless the
+  // caller's count is taken (the workspace query does not know the stride)
+  const bool far_rows = a->m >= sevo::kTileMinM && !(a->flags & SEVO_LINEAR_X_TILED) &&
+                        a->ldx > sevo::kTileMaxLdx;
+  const int k_splits = far_rows && (a->k_splits == 0 || a->m >= sevo::kLargeGemmMinM)
+                           ? 1 : a->k_splits;
+  sevo::LinearPlan plan =
+      sevo::plan_linear(a->m, a->n_out, a->k, k_splits, a->mode,
+                        far_rows ? sevo::kLinearSmallMb : sevo::kLinearMaxMb);
   size_t need = sevo::linear_workspace_bytes(a->m, a->n_out, plan);
   if (need > 0 && (!a->workspace || a->workspace_bytes < need)) {
     // a workspace sized for M tiles of 64 rows keeps them; from 256 rows on
     // none is required
     plan = a->m >= sevo::kLargeGemmMinM
                ? sevo::plan_linear(a->m, a->n_out, a->k, 0, a->mode, sevo::kLinearMaxMb, 1)
-               : sevo::plan_linear(a->m, a->n_out, a->k, a->k_splits, a->mode,
+               : sevo::plan_linear(a->m, a->n_out, a->k, k_splits, a->mode,
                                    sevo::kLinearSmallMb);
     need = sevo::linear_workspace_bytes(a->m, a->n_out, plan);
   }

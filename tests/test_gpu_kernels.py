@@ -643,6 +643,53 @@ def test_linear_tiles_at_their_edges(S, m, n_out, k, mode, xt):
                                        atol=2e-5 * np.sqrt(k) * 0.02 + 1e-6 * np.abs(y).max())
 
 
+@pytest.mark.parametrize("m,n_out,k,mode,pad", [
+    (65, 192, 64, 0, 8), (128, 320, 192, 2, 1024), (130, 128, 4160, 1, 256), (70, 512, 96, 0, 40),
+    (193, 24640, 128, 2, 64), (300, 24640, 64, 0, 200), (257, 192, 2080, 1, 96)])
+def test_linear_row_major_column_slice(S, m, n_out, k, mode, pad):
+    """X as the last k columns of a wider tensor (ldx = k + pad): its last row
+    ends with the allocation, and the columns before it are NaN.  The same bits
+    as of a contiguous X."""
+    sevo, _ = S
+    say(f"linear column slice m={m} n={n_out} k={k} mode={mode} ldx={k + pad}")
+    x, _, wp, _, _ = _linear_inputs(sevo, m, n_out, k, mode)
+    wide = torch.full((m, k + pad), float("nan"), dtype=torch.bfloat16, device="cuda")
+    wide[:, pad:] = x
+    out = [torch.full((m, n_out), 0.5, device="cuda") if mode == 1 else None for _ in range(2)]
+    a, b = (sevo.sevo_linear(t, wp, mode=mode, out=o) for t, o in zip((x, wide[:, pad:]), out))
+    torch.cuda.synchronize()
+    assert torch.isfinite(a.float()).all()
+    assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("m,k,ldx", [(65, 64, 1 << 27), (65, 1 << 25, 1 << 25),
+                                     (260, 1 << 25, 1 << 25)])
+def test_linear_rows_past_32_bit_offsets(S, m, k, ldx):
+    """A row stride or a K whose byte offsets pass 2^32 inside one 16- or 64-row
+    block: sums of a few weight columns, picked by ones in X."""
+    sevo, _ = S
+    n_out = 64
+    say(f"linear long rows m={m} k={k} ldx={ldx}")
+    w = torch.empty(n_out, k, dtype=torch.bfloat16, device="cuda")
+    sevo.sevo_fill_normal_bf16(w, synth.tensor_key(k, 57), 0, 1.0)
+    wp = sevo.sevo_pack_weight(w)
+    flat = torch.empty((m - 1) * ldx + k, dtype=torch.bfloat16, device="cuda")
+    x = flat.as_strided((m, k), (ldx, 1))
+    x.zero_()
+    g = np.random.default_rng(m)
+    cols = g.integers(0, k, (m, 3))
+    cols[0, 0], cols[1, 0] = 0, k - 1
+    rows = torch.arange(m, device="cuda")
+    ct = torch.from_numpy(cols).cuda()
+    for j in range(3):
+        x[rows, ct[:, j]] += 1
+    ref = sum(w[:, ct[:, j]].double() for j in range(3)).t().cpu().numpy()
+    del w
+    got = sevo.sevo_linear(x, wp)
+    torch.cuda.synchronize()
+    np.testing.assert_allclose(got.double().cpu().numpy(), ref, rtol=0, atol=1e-5)
+
+
 # one shape per instantiated skinny kernel: (M tile rows, 16-row weight blocks
 # per workgroup, SwiGLU pairs or not), found by running the planner over n_out;
 # every one leaves a ragged last workgroup (row blocks past the matrix)
