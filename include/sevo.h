@@ -495,8 +495,13 @@ sevo_status sevo_add_rmsnorm(float* x, const float* partials, int32_t n_partials
  *        SEVO_LINEAR_OUT_TILED   SWIGLU output in the tiled activation layout
  * k % 32 == 0; n_out % 64 == 0.  k_splits 0 = chosen by the library (SWIGLU
  * always uses one split; k_splits 1 is kept at every m, another count below m =
- * 256, where the library chooses from then on; there a workspace below
- * sevo_linear_workspace_bytes, or none, means one split). */
+ * 256, where the library chooses from then on).  The workspace is scratch for
+ * the split partials: calls that may overlap in time (other streams, other
+ * threads) each need their own.  A plan with splits may add in another order
+ * than one split, so the last bits can depend on the workspace given: below
+ * sevo_linear_workspace_bytes (none, or a misaligned one, included) a call of
+ * m >= 256 runs one split, and one of 65 <= m < 256 the plan of 64-row M tiles
+ * where the workspace holds its partials (else WORKSPACE_TOO_SMALL). */
 #define SEVO_LINEAR_STORE 0
 #define SEVO_LINEAR_ADD 1
 #define SEVO_LINEAR_SWIGLU 2

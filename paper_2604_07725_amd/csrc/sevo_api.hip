@@ -640,7 +640,9 @@ SEVO_API sevo_status sevo_linear(const sevo_linear_args* a, void* stream) {
       sevo::plan_linear(a->m, a->n_out, a->k, k_splits, a->mode,
                         far_rows ? sevo::kLinearSmallMb : sevo::kLinearMaxMb);
   size_t need = sevo::linear_workspace_bytes(a->m, a->n_out, plan);
-  if (need > 0 && (!a->workspace || a->workspace_bytes < need)) {
+  // a misaligned workspace counts as none, in every plan that can do without
+  const size_t room = a->workspace && aligned16(a->workspace) ? a->workspace_bytes : 0;
+  if (need > room) {
     // a workspace sized for M tiles of 64 rows keeps them; from 256 rows on
     // none is required
     plan = a->m >= sevo::kLargeGemmMinM
@@ -649,11 +651,9 @@ SEVO_API sevo_status sevo_linear(const sevo_linear_args* a, void* stream) {
                                    sevo::kLinearSmallMb);
     need = sevo::linear_workspace_bytes(a->m, a->n_out, plan);
   }
-  if (need > 0) {
-    if (!a->workspace || !aligned16(a->workspace) || a->workspace_bytes < need)
-      return fail(SEVO_ERR_WORKSPACE_TOO_SMALL, "linear needs %zu workspace bytes, got %zu", need,
-                  a->workspace_bytes);
-  }
+  if (need > room)
+    return fail(SEVO_ERR_WORKSPACE_TOO_SMALL,
+                "linear needs %zu bytes of 16-byte aligned workspace, got %zu", need, room);
   hipError_t e = sevo::launch_linear(
       a->m, a->n_out, a->k, a->ldx, (a->flags & SEVO_LINEAR_X_TILED) ? 1 : 0, a->mode, plan,
       static_cast<const sevo::bf16_t*>(a->x), static_cast<const sevo::bf16_t*>(a->w), a->out,

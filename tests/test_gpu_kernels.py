@@ -690,6 +690,33 @@ def test_linear_rows_past_32_bit_offsets(S, m, k, ldx):
     np.testing.assert_allclose(got.double().cpu().numpy(), ref, rtol=0, atol=1e-5)
 
 
+@pytest.mark.parametrize("m,n_out,k", [(512, 256, 4096), (257, 192, 2080), (65, 5184, 2048)])
+def test_linear_misaligned_workspace_counts_as_none(S, m, n_out, k):
+    """A workspace that is large enough but not 16-byte aligned is left alone by
+    a plan that can do without one (from 256 rows on, and below where the plan of
+    64-row tiles has one split): accepted, unwritten, the bits of one split."""
+    import ctypes as C
+    sevo, _ = S
+    say(f"linear misaligned workspace m={m} n={n_out} k={k}")
+    x, _, wp, _, _ = _linear_inputs(sevo, m, n_out, k, 0)
+    need = sevo.sevo_linear_workspace_bytes(m, n_out, k)
+    assert need > 0
+    ws = poisoned(need + 64)
+    out = torch.zeros(m, n_out, dtype=torch.float32, device="cuda")
+    a = sevo.LinearArgs(m=m, n_out=n_out, k=k, ldx=k, mode=0, k_splits=0, flags=0,
+                        x=x.data_ptr(), w=wp.data_ptr(), out=out.data_ptr(),
+                        workspace=ws.data_ptr() + 4, workspace_bytes=need + 32)
+    assert sevo.lib().sevo_linear(C.byref(a), None) == sevo.OK
+    torch.cuda.synchronize()
+    assert bool((ws == 255).all())
+    want = sevo.sevo_linear(x, wp, k_splits=1)
+    torch.cuda.synchronize()
+    if m >= 256:
+        assert torch.equal(out, want)
+    else:
+        assert float((out - want).abs().max()) <= 2e-5 * np.sqrt(k) * 0.02
+
+
 # one shape per instantiated skinny kernel: (M tile rows, 16-row weight blocks
 # per workgroup, SwiGLU pairs or not), found by running the planner over n_out;
 # every one leaves a ragged last workgroup (row blocks past the matrix)
