@@ -18,10 +18,12 @@ hipError_t launch_rmsnorm(const float* x, const bf16_t* gain, int rows, int cols
 // input), or row-major with out_tiled 0.  part is [S][rows][cols] fp32.
 // row_idx (optional): output row r takes source row row_idx[r] of x and of
 // the partials (which then have part_rows rows); x is not written back.
+// own_sum 1: the partials are summed by themselves, in order, and that sum added
+// to x (a prefill's split products and expert slots).
 hipError_t launch_add_rmsnorm(float* x, const float* part, int S, const bf16_t* gain, int rows,
                               int cols, float eps, bf16_t* out, hipStream_t st,
                               const int32_t* row_idx = nullptr, int part_rows = 0,
-                              int out_tiled = 1);
+                              int out_tiled = 1, int own_sum = 0);
 // per packed prefill token: page-table row (its sequence) and position
 hipError_t launch_prefill_index(const int32_t* seq_starts, const int32_t* start_pos, int n_seqs,
                                 int T, int32_t* row, int32_t* pos, hipStream_t st);

@@ -323,6 +323,10 @@ hipError_t launch_embed(const bf16_t* embed, const int32_t* tokens, int n, int h
 // pass with all split loads independent (latency, not bandwidth, is the cost).
 // With row_idx, output row r reads row row_idx[r] of x and the partials and
 // x is not written back (the final norm of a prefill's scored rows).
+// OWN_SUM: x += (the partials' sum), instead of the partials one by one: one
+// rounding at the size of x, and the bits of a sum that was formed elsewhere.
+// (A sum of its own starts at -0, which leaves the first partial's bits.)
+template <bool OWN_SUM>
 __global__ __launch_bounds__(1024) void add_rmsnorm_kernel(float* __restrict__ x,
                                                            const float* __restrict__ part, int S,
                                                            size_t part_stride,
@@ -342,9 +346,12 @@ __global__ __launch_bounds__(1024) void add_rmsnorm_kernel(float* __restrict__ x
 #pragma unroll
       for (int s = 0; s < 16; ++s)
         if (s < S) p[s] = *reinterpret_cast<const f32x4*>(pr + s * part_stride + c);
+      const f32x4 x0 = v;
+      if constexpr (OWN_SUM) v = f32x4{-0.f, -0.f, -0.f, -0.f};
 #pragma unroll
       for (int s = 0; s < 16; ++s)
         if (s < S) v += p[s];
+      if constexpr (OWN_SUM) v = x0 + v;
       if (!row_idx) *reinterpret_cast<f32x4*>(xr + c) = v;
     }
     return v;
@@ -381,14 +388,17 @@ __global__ __launch_bounds__(1024) void add_rmsnorm_kernel(float* __restrict__ x
   if (c1 < cols) store_out(c1, v1, inv);
   for (int c = c0 + 8192; c < cols; c += 4096) {
     f32x4 v = *reinterpret_cast<const f32x4*>(xr + c);
-    if (row_idx) {  // x was not updated in place: add the partials again, same order
+    if (row_idx && S > 0) {  // x was not updated in place: add the partials again, same order
       f32x4 p[16];
 #pragma unroll
       for (int s = 0; s < 16; ++s)
         if (s < S) p[s] = *reinterpret_cast<const f32x4*>(pr + s * part_stride + c);
+      const f32x4 x0 = v;
+      if constexpr (OWN_SUM) v = f32x4{-0.f, -0.f, -0.f, -0.f};
 #pragma unroll
       for (int s = 0; s < 16; ++s)
         if (s < S) v += p[s];
+      if constexpr (OWN_SUM) v = x0 + v;
     }
     store_out(c, v, inv);
   }
@@ -400,7 +410,7 @@ __global__ __launch_bounds__(1024) void add_rmsnorm_kernel(float* __restrict__ x
 // reduction.  The sum of squares is formed exactly as in the 1024-thread form:
 // the groups of its thread T = 256 (g % 4) + t in order, one wave sum per
 // wave of T, the 16 wave sums in order, so both forms give identical output.
-template <int NG>
+template <int NG, bool OWN_SUM>
 __global__ __launch_bounds__(256) void add_rmsnorm_rows_kernel(float* __restrict__ x,
                                                                const float* __restrict__ part,
                                                                int S, size_t part_stride,
@@ -423,6 +433,13 @@ __global__ __launch_bounds__(256) void add_rmsnorm_rows_kernel(float* __restrict
   }
   if (S > 0) {
     constexpr int kAtOnce = NG > 4 ? 2 : 4;  // partials loaded together, added in order
+    f32x4 x0[OWN_SUM ? NG : 1];
+    if constexpr (OWN_SUM)
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        x0[g] = v[g];
+        v[g] = f32x4{-0.f, -0.f, -0.f, -0.f};
+      }
     for (int s0 = 0; s0 < S; s0 += kAtOnce) {
       f32x4 p[kAtOnce][NG];
 #pragma unroll
@@ -442,6 +459,7 @@ __global__ __launch_bounds__(256) void add_rmsnorm_rows_kernel(float* __restrict
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
       const int c = 1024 * g + 4 * t;
+      if constexpr (OWN_SUM) v[g] = x0[g] + v[g];
       if (c < cols && !row_idx) *reinterpret_cast<f32x4*>(xr + c) = v[g];
     }
   }
@@ -478,25 +496,25 @@ __global__ __launch_bounds__(256) void add_rmsnorm_rows_kernel(float* __restrict
 
 hipError_t launch_add_rmsnorm(float* x, const float* part, int S, const bf16_t* gain, int rows,
                               int cols, float eps, bf16_t* out, hipStream_t st,
-                              const int32_t* row_idx, int part_rows, int out_tiled) {
+                              const int32_t* row_idx, int part_rows, int out_tiled, int own_sum) {
   if (rows == 0) return hipSuccess;
   if (S > 16) return hipErrorInvalidValue;
   const size_t stride = (size_t)(row_idx ? part_rows : rows) * cols;
   const int s_eff = part ? S : 0;
-  if (rows >= 512 && cols <= 8192) {
-    const int ng = (cols + 1023) / 1024;
-    auto go = [&](auto kern) {
-      hipLaunchKernelGGL(kern, dim3(rows), dim3(256), 0, st, x, part, s_eff, stride, gain,
-                         cols, eps, out, out_tiled, row_idx);
-    };
-    if (ng <= 2) go(add_rmsnorm_rows_kernel<2>);
-    else if (ng <= 4) go(add_rmsnorm_rows_kernel<4>);
-    else go(add_rmsnorm_rows_kernel<8>);
+  const bool many = rows >= 512 && cols <= 8192;
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(rows), dim3(many ? 256 : 1024), 0, st, x, part, s_eff, stride,
+                       gain, cols, eps, out, out_tiled, row_idx);
     return hipGetLastError();
-  }
-  hipLaunchKernelGGL(add_rmsnorm_kernel, dim3(rows), dim3(1024), 0, st, x, part, s_eff, stride,
-                     gain, cols, eps, out, out_tiled, row_idx);
-  return hipGetLastError();
+  };
+  own_sum = own_sum && s_eff > 1;
+  if (!many) return own_sum ? go(add_rmsnorm_kernel<true>) : go(add_rmsnorm_kernel<false>);
+  const int ng = (cols + 1023) / 1024;
+  if (ng <= 2)
+    return own_sum ? go(add_rmsnorm_rows_kernel<2, true>) : go(add_rmsnorm_rows_kernel<2, false>);
+  if (ng <= 4)
+    return own_sum ? go(add_rmsnorm_rows_kernel<4, true>) : go(add_rmsnorm_rows_kernel<4, false>);
+  return own_sum ? go(add_rmsnorm_rows_kernel<8, true>) : go(add_rmsnorm_rows_kernel<8, false>);
 }
 
 // Packed token t of a prefill batch -> its sequence s (the page-table row)

@@ -1316,9 +1316,10 @@ SEVO_API sevo_status sevo_prefill_confidence(sevo_model* m, const sevo_prefill_a
   // epilogue (the same single fp32 add as a separate residual update, without
   // a round trip of the product through memory); with K split, their partials
   // go to `part`, as a MoE FFN's slot-order sum does, and the next residual
-  // add + RMSNorm adds them to x.  A MoE FFN of one chunk leaves its k slots to
-  // that norm (the sum kernel's pass over them, its result written and read
-  // again: 8146 tokens at 30B-A3B widths 113 us per layer, the norm's extra 55)
+  // add + RMSNorm adds their sum to x.  A MoE FFN of one chunk leaves its k slots
+  // to that norm, which forms the same sum (the sum kernel's pass over them, its
+  // result written and read again: 8146 tokens at 30B-A3B widths 113 us per
+  // layer, the norm's extra 55)
   const bool moe = c.n_experts > 0;
   const bool one_chunk = moe && T <= L.mc;
   float* ffn_part = one_chunk ? reinterpret_cast<float*>(ws + L.m_slots) : part;
@@ -1328,7 +1329,7 @@ SEVO_API sevo_status sevo_prefill_confidence(sevo_model* m, const sevo_prefill_a
       ProfScope ps(SEVO_PROF_NORM, st);
       e = sevo::launch_add_rmsnorm(x, pending ? ffn_part : nullptr, pending,
                                    static_cast<const sevo::bf16_t*>(m->attn_norm[l]), T, H,
-                                   c.rms_eps, h, st);
+                                   c.rms_eps, h, st, nullptr, 0, 1, 1);
     }
     if (e == hipSuccess) {
       ProfScope ps(SEVO_PROF_QKV, st);
@@ -1359,8 +1360,9 @@ SEVO_API sevo_status sevo_prefill_confidence(sevo_model* m, const sevo_prefill_a
     }
     if (e == hipSuccess) {
       ProfScope ps(SEVO_PROF_NORM, st);
-      e = sevo::launch_add_rmsnorm(x, so ? part : nullptr, so, static_cast<const sevo::bf16_t*>(m->ffn_norm[l]),
-                                   T, H, c.rms_eps, h, st, nullptr, 0, moe ? 0 : 1);
+      e = sevo::launch_add_rmsnorm(x, so ? part : nullptr, so,
+                                   static_cast<const sevo::bf16_t*>(m->ffn_norm[l]), T, H,
+                                   c.rms_eps, h, st, nullptr, 0, moe ? 0 : 1, 1);
     }
     if (moe) {
       // the mixture of experts, a chunk of tokens at a time: per-slot outputs
@@ -1394,7 +1396,7 @@ SEVO_API sevo_status sevo_prefill_confidence(sevo_model* m, const sevo_prefill_a
       ProfScope ps(SEVO_PROF_NORM, st);
       e = sevo::launch_add_rmsnorm(x, pending ? ffn_part : nullptr, pending,
                                    static_cast<const sevo::bf16_t*>(m->final_norm), nr, H,
-                                   c.rms_eps, hf, st, a->scored_rows + r0, T);
+                                   c.rms_eps, hf, st, a->scored_rows + r0, T, 1, 1);
     }
     if (e == hipSuccess) {
       ProfScope ps(SEVO_PROF_LM_HEAD, st);

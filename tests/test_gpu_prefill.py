@@ -365,6 +365,24 @@ def test_prefill_confidence_tiny_moe_halved_down_tiles(S):
     assert np.abs(g_conf - conf).max() <= 1e-2
 
 
+def test_prefill_confidence_moe_chunk_does_not_change_the_bits(S):
+    """A token's expert outputs are summed in slot order before the residual add,
+    whether the next norm sums the slots (one chunk) or the chunks' sum kernel
+    does: every row's c, each C and every appended key and value of 2200 tokens
+    are the same bits in one chunk, in two and in three."""
+    shape, lens = synth.TINY_MOE, [1500, 700]
+    scored = list(range(40, 1500, 3)) + list(range(1520, 2200, 3))
+    say("prefill confidence (tiny MoE, one chunk against several)")
+    ref = None
+    for chunk in (0, 1104, 736):
+        (conf, row, pools), *_ = _engine_case(S, shape, 9, lens, scored, 20, moe_chunk=chunk)
+        ref = ref or (conf, row, pools)
+        np.testing.assert_array_equal(conf, ref[0])
+        np.testing.assert_array_equal(row, ref[1])
+        for a, b in zip(pools, ref[2]):
+            np.testing.assert_array_equal(a, b)
+
+
 @pytest.mark.parametrize("moe_chunk", [0, 256])
 def test_prefill_confidence_moe30b_reduced_depth(S, moe_chunk):
     """The 30B-A3B-class MoE widths (hidden 2048, 32/4 heads, 128 experts of
