@@ -293,6 +293,14 @@ sevo_status sevo_attn_prefill(const sevo_prefill_attn_args* a, void* stream);
  *   out_conf[s] = mean of c_r over the scored rows inside sequence s
  *                 (C(tau) of Eq. 2; 0 for a sequence without scored rows).
  * Only the scored rows go through the LM head (in chunks of 4096 rows).
+ * Sequences never interact, and the same call gives the same bits.  In calls of
+ * at least 4608 tokens a sequence's results are also the same bits whatever else
+ * the call holds, and whatever workspace_bytes and moe_chunk, except that a last
+ * LM-head chunk of at most 64 rows, and a MoE chunk with fewer than 24 n_experts /
+ * n_experts_active tokens (or at most 64), run the decode step's kernels, which
+ * add in another order.  Below 4608 tokens the projections may split their sums
+ * by the number of tokens and the room in the workspace: results then agree to
+ * the rounding of the bf16 storage points.
  *   tokens      int32 [total_tokens], sequences back to back
  *   seq_starts  int32 [n_seqs + 1] (device), start_pos int32 [n_seqs] (device)
  *               or NULL: as in sevo_attn_prefill; positions must be below the

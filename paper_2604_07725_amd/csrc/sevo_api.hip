@@ -1079,11 +1079,20 @@ struct PrefillLayout {
   int mc;  // tokens per MoE chunk
 };
 
+// From this many tokens on every projection of a prefill (the MoE router's too:
+// near ties of the routing would turn) runs one K split, so that a sequence's
+// bits do not depend on what else the call holds.  Splits are for calls with few
+// tiles (us, one split / split and sum: 512 x 4096 x 12288 78 / 58); up here the
+// idle CUs of a last round are all they save, and the partials' sum mostly takes
+// it back (7708 x 128 x 2048 15.1 / 15.4, 5050 x 5120 x 25600 1117 / 1105, but 7600
+// tokens 1759 / 1598).
+constexpr int kPrefillSplitTokens = 4608;
+
 // split false: no K splits (the sizes of a workspace without their partials)
 PrefillLayout prefill_layout(const sevo_model_config& c, int T, int R, int moe_chunk = 0,
                              bool split = true) {
   PrefillLayout L;
-  const int ms = split ? 16 : 1;
+  const int ms = split && T < kPrefillSplitTokens ? 16 : 1;
   auto plan = [&](int n_out, int k, int mode) {
     return sevo::plan_linear(T, n_out, k, 0, mode, sevo::kLinearMaxMb, ms);
   };
@@ -1134,7 +1143,7 @@ PrefillLayout prefill_layout(const sevo_model_config& c, int T, int R, int moe_c
     const size_t mc_cap = ((((size_t)1 << 31) - 1) / row_bytes) / 16 * 16;
     if (mc > mc_cap) mc = mc_cap;
     L.mc = (int)mc;
-    L.router_rows = split ? std::max(mc, std::min(mc, (size_t)4096) * 8) : mc;
+    L.router_rows = ms > 1 ? std::max(mc, std::min(mc, (size_t)4096) * 8) : mc;
     L.m_router = take(L.router_rows * E * 4);
     L.m_sel = take(mc * kk * 4);
     L.m_w = take(mc * kk * 4);
@@ -1186,8 +1195,10 @@ hipError_t run_moe_prefill_chunk(const sevo_model* m, int l, int c0, int nc,
   int32_t* asg = reinterpret_cast<int32_t*>(ws + L.m_assign);
   float* slots = reinterpret_cast<float*>(ws + L.m_slots);
   int32_t* tiles = reinterpret_cast<int32_t*>(ws + L.m_tiles);
-  const sevo::LinearPlan p_router = sevo::plan_linear(
-      nc, E, H, 0, SEVO_LINEAR_STORE, sevo::kLinearMaxMb, (int)std::min<size_t>(16, L.router_rows / nc));
+  const int router_splits = L.router_rows > (size_t)L.mc
+                                ? (int)std::min<size_t>(16, L.router_rows / nc) : 1;
+  const sevo::LinearPlan p_router = sevo::plan_linear(nc, E, H, 0, SEVO_LINEAR_STORE,
+                                                      sevo::kLinearMaxMb, router_splits);
   const bool grouped = (long long)nc * k >= (long long)kPrefillGroupedMinPerExpert * E;
   const int tile_rows = sevo::moe_group_rows((long long)nc * k, E);
   hipError_t e;

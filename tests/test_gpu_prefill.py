@@ -202,8 +202,9 @@ def test_prefill_confidence_full_size_batch_invariance(S):
     """The dense 8B engine at the benchmark's size (36 layers, 40960 tokens as
     sequences of 24576 and 16384, every row scored): each row's c equals, bit
     for bit, its value with the sequence run alone, and so does each C (rows
-    of different sequences never interact; a property at any size), all
-    finite, and C is the mean of its sequence's c."""
+    of different sequences never interact, and from 4608 tokens on no sum's
+    order depends on the call's size), all finite, and C is the mean of its
+    sequence's c."""
     sevo, di = S
     shape = synth.DENSE_8B
     lens = [24576, 16384]
@@ -241,6 +242,60 @@ def test_prefill_confidence_full_size_batch_invariance(S):
     np.testing.assert_array_equal(c01, np.concatenate([c0, c1]))
     np.testing.assert_allclose(c01, [r0.astype(np.float64).mean(), r1.astype(np.float64).mean()],
                                rtol=1e-5)
+
+
+@pytest.mark.parametrize("model,lens,bar", [("dense32b", [5000, 5100], 0.0),
+                                            ("moe30b", [5000, 5100], 0.0),
+                                            ("dense8b", [4608, 700], 0.0),
+                                            ("dense8b", [700, 400], 3e-2)])
+def test_prefill_confidence_batch_invariance(S, model, lens, bar):
+    """One layer of each class (vocabulary 4096): each sequence of at least 4608
+    tokens has the same bits alone and in the batch.  Smaller calls may split
+    their sums otherwise; they agree to the end-to-end bar of the widths."""
+    import dataclasses
+    sevo, di = S
+    base = {"dense32b": synth.DENSE_32B, "moe30b": synth.MOE_30B_A3B, "dense8b": synth.DENSE_8B}
+    shape = dataclasses.replace(base[model], n_layers=1, vocab=4096)
+    seed = 29
+    say(f"prefill batch invariance {model} {lens}")
+    pop = make_population(lens, shuffle=True, seed=seed)
+    rng = np.random.default_rng(seed)
+    toks = [rng.integers(0, shape.vocab, size=n).astype(np.int32) for n in lens]
+    model_h = sevo.sevo_init_model(shape, di.device_weights(shape, seed),
+                                   max_position=max(lens) + 1)
+    kvp = [torch.empty(pop.n_pages, shape.n_kv_heads, 2, 16 * shape.head_dim,
+                       dtype=torch.bfloat16, device="cuda")]
+
+    def run(seqs):
+        t = np.concatenate([toks[i] for i in seqs])
+        ss = np.concatenate([[0], np.cumsum([lens[i] for i in seqs])]).astype(np.int32)
+        rows = np.concatenate([np.arange(ss[j], ss[j + 1], 3) for j in range(len(seqs))])
+        kvp[0].zero_()
+        buf = sevo.PrefillBuffers(model_h, torch.from_numpy(t).cuda(), torch.from_numpy(ss).cuda(),
+                                  torch.from_numpy(np.ascontiguousarray(pop.page_table[seqs])
+                                                   .astype(np.int32)).cuda(), kvp,
+                                  torch.from_numpy(rows.astype(np.int32)).cuda(), 20,
+                                  max(lens[i] for i in seqs))
+        buf.run()
+        torch.cuda.synchronize()
+        return buf.out_conf.cpu().numpy(), buf.out_row_conf.cpu().numpy(), kvp[0].clone()
+
+    both_c, both_r, both_kv = run([0, 1])
+    at = 0
+    for i, n in enumerate(lens):
+        c, r, kv = run([i])
+        got = both_r[at:at + len(r)]
+        at += len(r)
+        assert np.isfinite(r).all()
+        if bar == 0.0 and n >= 4608:
+            np.testing.assert_array_equal(r, got)
+            np.testing.assert_array_equal(c, both_c[i:i + 1])
+            used = torch.from_numpy(pop.page_table[i][pop.page_table[i] >= 0].astype(np.int64)).cuda()
+            assert torch.equal(kv[used].view(torch.int16), both_kv[used].view(torch.int16))
+        else:
+            say(f"  sequence {i}: largest difference {np.abs(r - got).max():.2e}")
+            assert np.abs(r - got).max() <= (bar or 3e-2)
+    model_h.close()
 
 
 def test_prefill_confidence_tiny_matches_oracle(S):
