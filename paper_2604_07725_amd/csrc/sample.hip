@@ -688,8 +688,9 @@ __global__ __launch_bounds__(256) void sample_trunc_final_kernel(
 // with four tiles, 185 with nineteen).  Below four tiles each the longer chunks
 // only idle CUs (64 rows at T = 1: 31 us with one tile, 49 with two).
 constexpr int kTiledGroups = 2048;
-static int sample_tiles(int n, int vocab) {
-  const long long row = (vocab + kSampleChunk - 1) / kSampleChunk;
+static int row_tiles_of(int vocab) { return (vocab + kSampleChunk - 1) / kSampleChunk; }
+static int sample_tiles(int n, int row_tiles) {
+  const long long row = row_tiles;
   if (n * row < 4 * kTiledGroups) return 1;
   const long long chunks = std::min<long long>(row, (kTiledGroups + n - 1) / n);
   return (int)((row + chunks - 1) / chunks);
@@ -704,12 +705,12 @@ static size_t list_bytes(int n, int nchunks) {
 }
 
 size_t sample_workspace_bytes(int n, int vocab) {
-  const int nchunks = (vocab + kSampleChunk - 1) / kSampleChunk;
+  const int nchunks = row_tiles_of(vocab);
   return partial_bytes(n, nchunks) + 2 * list_bytes(n, nchunks);
 }
 
 bool sample_conf_supported(int vocab, int list_len) {
-  const int nchunks = (vocab + kSampleChunk - 1) / kSampleChunk;
+  const int nchunks = row_tiles_of(vocab);
   return list_len >= 0 && list_len <= kConfMaxK && list_len <= vocab &&
          (size_t)nchunks * list_len <= (size_t)4 * kWave * kConfMergeNV;
 }
@@ -720,8 +721,8 @@ hipError_t launch_logprob_sample(const float* logits, int n, int vocab, int64_t 
                                  int conf_k, float* out_conf, float* conf_sum, hipStream_t st,
                                  int top_k, float top_p, float min_p) {
   if (n == 0) return hipSuccess;
-  const int tiles = sample_tiles(n, vocab);
-  const int nchunks = (vocab + tiles * kSampleChunk - 1) / (tiles * kSampleChunk);
+  const int row_tiles = row_tiles_of(vocab), tiles = sample_tiles(n, row_tiles);
+  const int nchunks = (row_tiles + tiles - 1) / tiles;
   SamplePartial* part = reinterpret_cast<SamplePartial*>(workspace);
   char* lists = reinterpret_cast<char*>(workspace) + partial_bytes(n, nchunks);
   float* topk = reinterpret_cast<float*>(lists);

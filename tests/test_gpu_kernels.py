@@ -473,6 +473,23 @@ def test_sampler_lists_at_tile_and_list_edges(S, n, vocab, k):
     check_ids(got[:n], lps.cpu().numpy()[:n], rid, rlp, gap, det, label="lists")
 
 
+@pytest.mark.parametrize("temp", [0.0, 1.0])
+def test_sampler_at_the_largest_vocabulary(S, temp):
+    """2^31 - 4096 entries of one row (8.6 GB), where a chunk's end counted in
+    entries passes the largest int: the one large logit, near the end, wins, and
+    its log-probability is -log(1 + (V - 1) e^-40) = -9.1e-9, rounded to 0."""
+    sevo, _ = S
+    vocab = (1 << 31) - 4096
+    say(f"sampler, {vocab} entries, T = {temp}")
+    x = torch.zeros(1, vocab, device="cuda")
+    x[0, vocab - 5] = 40.0
+    one = torch.ones(1, dtype=torch.int64, device="cuda")
+    ids, lps = sevo.sevo_logprob_sample(x, temp, 5, one, one.int())
+    torch.cuda.synchronize()
+    assert ids.item() == vocab - 5
+    assert abs(lps.item()) <= 4e-6     # two roundings at 40
+
+
 def test_group_confidence_matches_oracle(S):
     sevo, _ = S
     rng = np.random.default_rng(3)
