@@ -1,14 +1,16 @@
 // Fused full-vocabulary log-softmax + Gumbel-max sampling.
 //
 // Pass 1: one 256-thread workgroup per (vocab chunk, candidate); a chunk is
-// one or more 4096-entry tiles.  Thread t owns the 4-entry groups 1024 r + 4 t
+// one or more 4096-entry tiles, each with a partial of its own (how many tiles a
+// workgroup walks depends on the number of rows; the order of no sum does).
+// Thread t owns the 4-entry groups 1024 r + 4 t
 // (r < 4) of a tile, each one Philox4x32-10 counter and one 16-byte load; it
 // computes z = logit / T, the running max and sum of exp(z - max) (reduced
 // over the wave in registers, then through LDS), and the best perturbed value
 // z + G (ties -> lowest index).  The
 // temperature mode (T = 0, T = 1, other) is a template parameter, so greedy
 // sampling carries no noise or division code.  Pass 2: one workgroup per
-// candidate merges its chunks in a fixed order and writes the token id and
+// candidate merges its tiles in a fixed order and writes the token id and
 // log-probability z_id - logsumexp(z).
 //
 // Optionally (conf_k > 0) the same passes produce the per-token confidence of
@@ -52,9 +54,9 @@ __device__ __forceinline__ float gumbel_from_bits(uint32_t w) {
 }
 
 struct SamplePartial {
-  float m;     // max z in the chunk
+  float m;     // max z in the tile
   float s;     // sum exp(z - m)
-  float best;  // best perturbed value
+  float best;  // best perturbed value of the chunk (in its first tile; else -inf)
   int idx;     // its vocab index
   float m1;    // max and sum exp of the raw logits (T = 1), for the confidence
   float s1;
@@ -268,16 +270,17 @@ __device__ __forceinline__ bool better(float a, int ia, float b, int ib) {
   return a > b || (a == b && ia < ib);
 }
 
+// (m, s) over a wave: the maximum is found first, so each lane rescales once
+__device__ __forceinline__ void wave_lse(float& m, float& s) {
+  const float M = wave_max(m);
+  s = wave_sum(m == -INFINITY ? 0.f : s * exp_le0(m - M));
+  m = M;
+}
+
 // RAW: the raw-logit statistics (m1, s1) differ from z's and are merged too;
-// otherwise they are set equal to the merged (m, s).  Within a wave the
-// maximum is found first, so each lane rescales its sum once.
+// otherwise they are set equal to the merged (m, s).
 template <int NW, bool RAW = true>
 __device__ __forceinline__ SamplePartial block_merge(SamplePartial p, SamplePartial* red) {
-  auto wave_lse = [](float& m, float& s) {
-    const float M = wave_max(m);
-    s = wave_sum(m == -INFINITY ? 0.f : s * exp_le0(m - M));
-    m = M;
-  };
   wave_lse(p.m, p.s);
   if constexpr (RAW) wave_lse(p.m1, p.s1);
   const float B = wave_max(p.best);
@@ -343,25 +346,71 @@ __device__ __forceinline__ float max16(const float (&x)[16]) {
   return t;
 }
 
-// adds 16 values, t their largest, to a running max and sum of exp(x - max);
-// values without a comparable one among them (all -inf or NaN) add nothing
-__device__ __forceinline__ void lse16(const float (&x)[16], float t, float& m, float& s) {
-  if (t == -INFINITY) return;
-  const float M = fmaxf(m, t);
-  s = m == -INFINITY ? 0.f : s * exp_le0(m - M);
+// max and sum of exp(x - max) of 16 values, t their largest; values without a
+// comparable one among them (all -inf or NaN) give an empty sum
+__device__ __forceinline__ float2 lse16(const float (&x)[16], float t) {
+  if (t == -INFINITY) return float2{-INFINITY, 0.f};
+  float s = 0.f;
 #pragma unroll
-  for (int e = 0; e < 16; ++e) s += exp_le0(x[e] - M);  // exp(-inf) = 0
-  m = M;
+  for (int e = 0; e < 16; ++e) s += exp_le0(x[e] - t);  // exp(-inf) = 0
+  return float2{t, s};
 }
+
+// The waves' (m, s) of each tile that a workgroup walks (and of the raw logits).
+// A tile is merged over the lanes, then over the four waves, whatever else the
+// workgroup holds; carried over its tiles instead, the last bits of the
+// log-probabilities and confidences followed the number of rows (greedy with the
+// confidence over 152K logits, us, carried / per tile: 1121 rows 163 / 169, 1927
+// 266 / 266, 4096 513 / 504).
+constexpr int kMaxTiles = kWave;
+template <bool RAW>
+struct TileSums {
+  float2 z[kMaxTiles][4];
+  float2 raw[RAW ? kMaxTiles : 1][4];
+  float best[4];
+  int idx[4];
+
+  __device__ __forceinline__ void put(float2 (&to)[4], float2 v) {
+    wave_lse(v.x, v.y);
+    if ((threadIdx.x & 63) == 0) to[threadIdx.x >> 6] = v;
+  }
+  __device__ __forceinline__ void put_best(float b, int i) {
+    const float B = wave_max(b);
+    i = wave_min(b == B ? i : kNoIndex);
+    if ((threadIdx.x & 63) == 0) best[threadIdx.x >> 6] = B, idx[threadIdx.x >> 6] = i;
+  }
+  static __device__ __forceinline__ float2 merged(const float2 (&w)[4]) {
+    float2 r = w[0];
+#pragma unroll
+    for (int k = 1; k < 4; ++k) lse_merge(r.x, r.y, w[k].x, w[k].y);
+    return r;
+  }
+  // after a barrier, by one wave: the partials of the chunk's n tiles
+  __device__ __forceinline__ void store(SamplePartial* out, int n) {
+    const int t = threadIdx.x & 63;
+    if (t >= n) return;
+    const float2 zs = merged(z[t]);
+    const float2 rs = RAW ? merged(raw[t]) : zs;
+    SamplePartial p{zs.x, zs.y, -INFINITY, kNoIndex, rs.x, rs.y};
+    if (t == 0)
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (better(best[k], idx[k], p.best, p.idx)) p.best = best[k], p.idx = idx[k];
+    out[t] = p;
+  }
+};
 
 // Pass 1.  MODE 0: T = 0 (greedy, no noise, z = x); 1: T = 1 (z = x); 2: any
 // other T (z = x / T).  CONF: also the chunk's conf_k largest raw logits.
 template <int MODE, bool CONF>
 __global__ __launch_bounds__(256) void sample_partial_kernel(
-    const float* __restrict__ logits, int vocab, int64_t ld, int tiles, float temp, uint64_t seed,
-    const uint64_t* __restrict__ uid, const int32_t* __restrict__ positions,
+    const float* __restrict__ logits, int vocab, int64_t ld, int row_tiles, int tiles, float temp,
+    uint64_t seed, const uint64_t* __restrict__ uid, const int32_t* __restrict__ positions,
     SamplePartial* __restrict__ part, int conf_k, float* __restrict__ topk) {
-  __shared__ SamplePartial red[4];
+  // for MODE 2 with the confidence also the statistics of the raw logits
+  // (T = 1), else they are z's
+  constexpr bool kRaw = MODE == 2 && CONF;
+  __shared__ TileSums<kRaw> sums;
   __shared__ float wtop[4][kConfMaxK];
   __shared__ float cand[4][kWave];
   const int chunk = blockIdx.x;
@@ -375,28 +424,25 @@ __global__ __launch_bounds__(256) void sample_partial_kernel(
     pos = (uint32_t)positions[i];
   }
   const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
-  // for MODE 2 with the confidence also the statistics of the raw logits
-  // (T = 1), else they are z's
-  constexpr bool kRaw = MODE == 2 && CONF;
-  SamplePartial p{-INFINITY, 0.f, -INFINITY, kNoIndex, -INFINITY, 0.f};
+  float best = -INFINITY;
+  int bidx = kNoIndex;
   TopList<float> list{cand[wave], conf_k};
   int best_base = 0;  // MODE 0: the tile of this lane's first largest value
   float next[16];
   load_tile(row, chunk * tiles * kSampleChunk, vocab, next);
-  for (int t = 0; t < tiles; ++t) {
+  const int nt = min(tiles, row_tiles - chunk * tiles);
+  for (int t = 0; t < nt; ++t) {
     const int base = (chunk * tiles + t) * kSampleChunk;
-    if (base >= vocab) break;
     float raw[16], z[16];
 #pragma unroll
     for (int e = 0; e < 16; ++e) raw[e] = next[e];
-    if (t + 1 < tiles && base + kSampleChunk < vocab)
-      load_tile(row, base + kSampleChunk, vocab, next);
+    if (t + 1 < nt) load_tile(row, base + kSampleChunk, vocab, next);
 #pragma unroll
     for (int e = 0; e < 16; ++e) z[e] = MODE == 2 ? raw[e] / temp : raw[e];
     const float zmax = max16(z);
     if constexpr (MODE == 0) {
-      if (zmax > p.best) {
-        p.best = zmax;
+      if (zmax > best) {
+        best = zmax;
         best_base = base;
       }
     } else {
@@ -417,31 +463,32 @@ __global__ __launch_bounds__(256) void sample_partial_kernel(
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const float pv = z[4 * r + e] + g[e];
-          if (v0 + e < vocab && pv > p.best) {
-            p.best = pv;
-            p.idx = v0 + e;
+          if (v0 + e < vocab && pv > best) {
+            best = pv;
+            bidx = v0 + e;
           }
         }
       }
     }
-    lse16(z, zmax, p.m, p.s);
+    sums.put(sums.z[t], lse16(z, zmax));
     const float rmax = kRaw ? max16(raw) : zmax;
-    if constexpr (kRaw) lse16(raw, rmax, p.m1, p.s1);
+    if constexpr (kRaw) sums.put(sums.raw[t], lse16(raw, rmax));
     if constexpr (CONF) list.add(raw, rmax, t == 0);
   }
   if constexpr (MODE == 0) {
     // the index of the largest value: its first place in the lane's tile
-    if (p.best > -INFINITY) {
+    if (best > -INFINITY) {
       if (tiles > 1) load_tile(row, best_base, vocab, next);
 #pragma unroll
       for (int e = 15; e >= 0; --e)
-        if (next[e] == p.best) p.idx = best_base + ((e >> 2) * 256 + threadIdx.x) * 4 + (e & 3);
+        if (next[e] == best) bidx = best_base + ((e >> 2) * 256 + threadIdx.x) * 4 + (e & 3);
     }
   }
   if constexpr (CONF) list.finish(wtop[wave]);
-  p = block_merge<4, kRaw>(p, red);  // its barrier also orders the four lists
+  sums.put_best(best, bidx);
+  __syncthreads();  // orders the sums, the bests and the four lists
   if (wave != 0) return;
-  if (lane == 0) part[(size_t)i * gridDim.x + chunk] = p;
+  sums.store(part + (size_t)i * row_tiles + chunk * tiles, nt);
   if constexpr (CONF) {
     const float v = merge4_desc(&wtop[0][0], conf_k);
     if (lane < conf_k) topk[((size_t)i * gridDim.x + chunk) * kConfMaxK + lane] = v;
@@ -480,17 +527,17 @@ __device__ __forceinline__ void merge_lists(int nchunks, int L, Get get, T* out,
 }
 
 __global__ __launch_bounds__(256) void sample_final_kernel(
-    const SamplePartial* __restrict__ part, int nchunks, const float* __restrict__ logits,
-    int vocab, int64_t ld, float temp, int32_t* __restrict__ out_tokens, float* __restrict__ out_lp,
-    int conf_k, const float* __restrict__ topk, float* __restrict__ out_conf,
+    const SamplePartial* __restrict__ part, int row_tiles, int nchunks,
+    const float* __restrict__ logits, int vocab, int64_t ld, float temp,
+    int32_t* __restrict__ out_tokens, float* __restrict__ out_lp, int conf_k, const float* __restrict__ topk, float* __restrict__ out_conf,
     float* __restrict__ conf_sum) {
   __shared__ SamplePartial red[4];
   __shared__ float wtop[4][kConfMaxK];
   __shared__ float cand[4][kWave];
   const int i = blockIdx.x;
   SamplePartial p{-INFINITY, 0.f, -INFINITY, kNoIndex, -INFINITY, 0.f};
-  for (int c = threadIdx.x; c < nchunks; c += 256) {
-    const SamplePartial o = part[(size_t)i * nchunks + c];
+  for (int c = threadIdx.x; c < row_tiles; c += 256) {
+    const SamplePartial o = part[(size_t)i * row_tiles + c];
     lse_merge(p.m, p.s, o.m, o.s);
     lse_merge(p.m1, p.s1, o.m1, o.s1);
     if (better(o.best, o.idx, p.best, p.idx)) {
@@ -555,29 +602,27 @@ __global__ __launch_bounds__(256) void group_confidence_kernel(
 // as the full sampler), lp = z_id - logsumexp(kept z).  T = 0: the first entry,
 // with the truncation and lp evaluated at T = 1.
 __global__ __launch_bounds__(256) void sample_trunc_partial_kernel(
-    const float* __restrict__ logits, int vocab, int64_t ld, int tiles, int L,
+    const float* __restrict__ logits, int vocab, int64_t ld, int row_tiles, int tiles, int L,
     SamplePartial* __restrict__ part, float* __restrict__ topv, int* __restrict__ topi) {
-  __shared__ SamplePartial red[4];
+  __shared__ TileSums<false> sums;
   __shared__ pair_key wtop[4][kConfMaxK];
   __shared__ pair_key cand[4][kWave];
   const int chunk = blockIdx.x;
   const int i = blockIdx.y;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const float* row = logits + (size_t)i * ld;
-  SamplePartial p{-INFINITY, 0.f, -INFINITY, kNoIndex, -INFINITY, 0.f};
   TopList<pair_key> list{cand[wave], L};
   float next[16];
   load_tile(row, chunk * tiles * kSampleChunk, vocab, next);
-  for (int t = 0; t < tiles; ++t) {
+  const int nt = min(tiles, row_tiles - chunk * tiles);
+  for (int t = 0; t < nt; ++t) {
     const int base = (chunk * tiles + t) * kSampleChunk;
-    if (base >= vocab) break;
     float x[16];
 #pragma unroll
     for (int e = 0; e < 16; ++e) x[e] = next[e];
-    if (t + 1 < tiles && base + kSampleChunk < vocab)
-      load_tile(row, base + kSampleChunk, vocab, next);
+    if (t + 1 < nt) load_tile(row, base + kSampleChunk, vocab, next);
     const float xmax = max16(x);
-    lse16(x, xmax, p.m, p.s);
+    sums.put(sums.z[t], lse16(x, xmax));
     pair_key key[16];
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
@@ -588,9 +633,10 @@ __global__ __launch_bounds__(256) void sample_trunc_partial_kernel(
     list.add(key, xmax, t == 0);
   }
   list.finish(wtop[wave]);
-  p = block_merge<4, false>(p, red);  // its barrier also orders the four lists
+  sums.put_best(-INFINITY, kNoIndex);
+  __syncthreads();  // orders the sums and the four lists
   if (wave != 0) return;
-  if (lane == 0) part[(size_t)i * gridDim.x + chunk] = p;
+  sums.store(part + (size_t)i * row_tiles + chunk * tiles, nt);
   const pair_key k = merge4_desc(&wtop[0][0], L);
   const size_t o = ((size_t)i * gridDim.x + chunk) * kConfMaxK;
   if (lane < L) {
@@ -600,7 +646,8 @@ __global__ __launch_bounds__(256) void sample_trunc_partial_kernel(
 }
 
 __global__ __launch_bounds__(256) void sample_trunc_final_kernel(
-    const SamplePartial* __restrict__ part, int nchunks, int L, const float* __restrict__ topv,
+    const SamplePartial* __restrict__ part, int row_tiles, int nchunks, int L,
+    const float* __restrict__ topv,
     const int* __restrict__ topi, float temp, int top_k, float top_p, float min_p, uint64_t seed,
     const uint64_t* __restrict__ uid, const int32_t* __restrict__ positions,
     int32_t* __restrict__ out_tokens, float* __restrict__ out_lp, int conf_k,
@@ -612,8 +659,8 @@ __global__ __launch_bounds__(256) void sample_trunc_final_kernel(
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   // logsumexp of the raw logits (confidence)
   SamplePartial p{-INFINITY, 0.f, -INFINITY, kNoIndex, -INFINITY, 0.f};
-  for (int c = threadIdx.x; c < nchunks; c += 256) {
-    const SamplePartial o = part[(size_t)i * nchunks + c];
+  for (int c = threadIdx.x; c < row_tiles; c += 256) {
+    const SamplePartial o = part[(size_t)i * row_tiles + c];
     lse_merge(p.m, p.s, o.m, o.s);
   }
   // merge the chunks' lists: a quarter per wave, then wave 0 merges the four
@@ -690,10 +737,10 @@ __global__ __launch_bounds__(256) void sample_trunc_final_kernel(
 constexpr int kTiledGroups = 2048;
 static int row_tiles_of(int vocab) { return (vocab + kSampleChunk - 1) / kSampleChunk; }
 static int sample_tiles(int n, int row_tiles) {
-  const long long row = row_tiles;
-  if (n * row < 4 * kTiledGroups) return 1;
-  const long long chunks = std::min<long long>(row, (kTiledGroups + n - 1) / n);
-  return (int)((row + chunks - 1) / chunks);
+  if ((long long)n * row_tiles < 4 * kTiledGroups) return 1;
+  const int chunks = std::max(std::min(row_tiles, (kTiledGroups + n - 1) / n),
+                              (row_tiles + kMaxTiles - 1) / kMaxTiles);
+  return (row_tiles + chunks - 1) / chunks;
 }
 
 static size_t partial_bytes(int n, int nchunks) {
@@ -723,22 +770,22 @@ hipError_t launch_logprob_sample(const float* logits, int n, int vocab, int64_t 
   if (n == 0) return hipSuccess;
   const int row_tiles = row_tiles_of(vocab), tiles = sample_tiles(n, row_tiles);
   const int nchunks = (row_tiles + tiles - 1) / tiles;
-  SamplePartial* part = reinterpret_cast<SamplePartial*>(workspace);
-  char* lists = reinterpret_cast<char*>(workspace) + partial_bytes(n, nchunks);
+  SamplePartial* part = reinterpret_cast<SamplePartial*>(workspace);  // per tile
+  char* lists = reinterpret_cast<char*>(workspace) + partial_bytes(n, row_tiles);
   float* topk = reinterpret_cast<float*>(lists);
   int* topi = reinterpret_cast<int*>(lists + list_bytes(n, nchunks));
   if (top_k > 0) {
     const int L = top_k > conf_k ? top_k : conf_k;
     hipLaunchKernelGGL(sample_trunc_partial_kernel, dim3(nchunks, n), dim3(256), 0, st, logits,
-                       vocab, ld, tiles, L, part, topk, topi);
+                       vocab, ld, row_tiles, tiles, L, part, topk, topi);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(sample_trunc_final_kernel, dim3(n), dim3(256), 0, st, part, nchunks, L,
-                       topk, topi, temp, top_k, top_p, min_p, seed, uid, positions, out_tokens,
-                       out_lp, conf_k, out_conf, conf_sum);
+    hipLaunchKernelGGL(sample_trunc_final_kernel, dim3(n), dim3(256), 0, st, part, row_tiles,
+                       nchunks, L, topk, topi, temp, top_k, top_p, min_p, seed, uid, positions,
+                       out_tokens, out_lp, conf_k, out_conf, conf_sum);
     return hipGetLastError();
   }
-  using PartialFn = void (*)(const float*, int, int64_t, int, float, uint64_t, const uint64_t*,
+  using PartialFn = void (*)(const float*, int, int64_t, int, int, float, uint64_t, const uint64_t*,
                             const int32_t*, SamplePartial*, int, float*);
   static constexpr PartialFn kPartial[3][2] = {
       {sample_partial_kernel<0, false>, sample_partial_kernel<0, true>},
@@ -746,11 +793,12 @@ hipError_t launch_logprob_sample(const float* logits, int n, int vocab, int64_t 
       {sample_partial_kernel<2, false>, sample_partial_kernel<2, true>}};
   const int mode = temp == 0.f ? 0 : temp == 1.f ? 1 : 2;
   hipLaunchKernelGGL(kPartial[mode][conf_k > 0 ? 1 : 0], dim3(nchunks, n), dim3(256), 0, st,
-                     logits, vocab, ld, tiles, temp, seed, uid, positions, part, conf_k, topk);
+                     logits, vocab, ld, row_tiles, tiles, temp, seed, uid, positions, part, conf_k,
+                     topk);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(sample_final_kernel, dim3(n), dim3(256), 0, st, part, nchunks, logits, vocab,
-                     ld, temp, out_tokens, out_lp, conf_k, topk, out_conf, conf_sum);
+  hipLaunchKernelGGL(sample_final_kernel, dim3(n), dim3(256), 0, st, part, row_tiles, nchunks,
+                     logits, vocab, ld, temp, out_tokens, out_lp, conf_k, topk, out_conf, conf_sum);
   return hipGetLastError();
 }
 

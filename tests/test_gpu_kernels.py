@@ -490,6 +490,31 @@ def test_sampler_at_the_largest_vocabulary(S, temp):
     assert abs(lps.item()) <= 4e-6     # two roundings at 40
 
 
+@pytest.mark.parametrize("temp,top_k,conf", [(0.0, 0, 20), (1.0, 0, 0), (0.7, 0, 20), (0.7, 20, 20)])
+def test_sampler_rows_do_not_depend_on_the_batch(S, temp, top_k, conf):
+    """1200 rows of 152K logits, whose workgroups walk many tiles each, against
+    the first and last 30 of them alone (one tile each): the same ids,
+    log-probabilities and confidences, bit for bit."""
+    sevo, _ = S
+    n, vocab = 1200, 151936
+    say(f"sampler batch invariance T={temp} top_k={top_k} conf={conf}")
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randn(n, vocab, device="cuda", generator=g) * 2.0
+    uid = torch.arange(n, dtype=torch.int64, device="cuda") * 977 + 1
+    pos = torch.arange(n, dtype=torch.int32, device="cuda")
+
+    def run(a, b):
+        out = sevo.sevo_logprob_sample(x[a:b], temp, 7, uid[a:b].clone(), pos[a:b].clone(),
+                                       conf_topk=conf, top_k=top_k, top_p=0.9 if top_k else 1.0)
+        torch.cuda.synchronize()
+        return [t.cpu().numpy() for t in out]
+
+    whole = run(0, n)
+    for a, b in ((0, 30), (n - 30, n)):
+        for w, p in zip(whole, run(a, b)):
+            np.testing.assert_array_equal(w[a:b], p)
+
+
 def test_group_confidence_matches_oracle(S):
     sevo, _ = S
     rng = np.random.default_rng(3)
