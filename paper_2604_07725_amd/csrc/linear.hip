@@ -274,12 +274,13 @@ static int pick_mb(int m, int n_out, int k, int max_mb) {
 
 // Row blocks per workgroup with an instantiated kernel: at least 3 for a
 // 64-row M tile (fewer re-read each activation fragment for too few weight
-// fragments), at most what the registers hold; SwiGLU takes whole pairs.
+// fragments), at most what the registers hold; SwiGLU takes whole pairs, and
+// only it comes in eight activation blocks.
 constexpr int rb_min(int mb) { return mb >= 4 ? 3 : 2; }
 constexpr int rb_max(int mb) { return mb == 8 ? 6 : (mb == 4 ? 8 : (mb == 2 ? 12 : 16)); }
 static const int kRbSet[] = {2, 3, 4, 5, 6, 8, 10, 12, 14, 16};
 constexpr bool rb_ok(int rb, int mb, int swiglu) {
-  return rb >= rb_min(mb) && rb <= rb_max(mb) && (!swiglu || rb % 2 == 0);
+  return rb >= rb_min(mb) && rb <= rb_max(mb) && (swiglu ? rb % 2 == 0 : mb < 8);
 }
 
 LinearPlan plan_linear(int m, int n_out, int k, int k_splits, int mode, int max_mb,
@@ -295,9 +296,9 @@ LinearPlan plan_linear(int m, int n_out, int k, int k_splits, int mode, int max_
       !(mode == 2 && m <= 128 && n_out < 192 * 256))
     return plan_tiles(m, n_out, k, mode, m < kLargeGemmMinM || k_splits == 1 ? k_splits : 0,
                       max_splits);
-  const int mb = pick_mb(m, n_out, k, max_mb);
-  const int mt = (m + 16 * mb - 1) / (16 * mb);
   const int swiglu = mode == 2;
+  const int mb = pick_mb(m, n_out, k, swiglu ? max_mb : kLinearSmallMb);
+  const int mt = (m + 16 * mb - 1) / (16 * mb);
   const int per_unit = swiglu ? 2 : 1;  // row blocks per unit (a gate/up pair)
   const int units = (n_out / 16) / per_unit;
   auto chunk_of = [&](int s) {

@@ -759,7 +759,26 @@ def test_linear_misaligned_workspace_counts_as_none(S, m, n_out, k):
         assert float((out - want).abs().max()) <= 2e-5 * np.sqrt(k) * 0.02
 
 
-# one shape per instantiated skinny kernel: (M tile rows, 16-row weight blocks
+@pytest.mark.parametrize("m,n_out,k,rb", [(65, 1024, 32768, 4), (128, 1024, 32768, 4),
+                                          (70, 16448, 2048, 6), (128, 16448, 2048, 6)])
+def test_linear_eight_block_kernels(S, m, n_out, k, rb):
+    """Both eight-block kernels (gate/up matrices of 64 MB or more at 65..128
+    rows), the second with a ragged last workgroup, against float64 products of
+    sampled columns."""
+    sevo, _ = S
+    assert sevo.sevo_linear_plan(m, n_out, k, 0, 2)[2] == rb
+    say(f"linear eight blocks m={m} n={n_out} k={k}")
+    x, _, wp, xh, wh = _linear_inputs(sevo, m, n_out, k, 2)
+    F = n_out // 2
+    cols = np.unique(np.concatenate([np.arange(0, F, 7), [F - 1]]))
+    xd = xh.astype(np.float64)
+    y = od.silu(xd @ wh[cols].astype(np.float64).T) * (xd @ wh[F + cols].astype(np.float64).T)
+    got = to_np(sevo.sevo_linear(x, wp, mode=2))[:, cols]
+    # one bf16 rounding of the product plus fp32 accumulation error
+    assert np.all(np.abs(got - y) <= 2 ** -8 * np.abs(y) + 1e-4 * np.abs(y).max())
+
+
+# one shape per instantiated skinny kernel of at most 64 rows: (M tile rows, 16-row weight blocks
 # per workgroup, SwiGLU pairs or not), found by running the planner over n_out;
 # every one leaves a ragged last workgroup (row blocks past the matrix)
 ROW_BLOCK_CASES = [
