@@ -208,6 +208,10 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 ? 2 : 1)) void attn_prefill_kerne
           if (64 * b + 16 * j + sl >= nkeys)
             so[j * PAGE_ELEMS + (e * 2 + ((sl >> 3) ^ pf_vswz(e))) * 8 + (sl & 7)] = 0;
       }
+      // this wave's zeros have landed (the barrier alone waits for nothing); with
+      // the builtin the compiler, its count of pending loads disturbed, drained
+      // the later stages' direct loads in every block (40K tokens 2% slower)
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       lds_barrier();
     }
     if (active && b <= last_b) {
