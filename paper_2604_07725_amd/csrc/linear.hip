@@ -30,6 +30,8 @@
 //     superblock holds 32 gate rows followed by the matching 32 up rows, so
 //     row blocks (h, h + 2) of superblock s are gate and up of output columns
 //     32 s + 16 h .. + 15, and it writes silu(g) * u.
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -285,6 +287,7 @@ constexpr bool rb_ok(int rb, int mb, int swiglu) {
 
 LinearPlan plan_linear(int m, int n_out, int k, int k_splits, int mode, int max_mb,
                        int max_splits) {
+  if (k_splits > k / 32) k_splits = std::max(k / 32, 1);  // (a chunk is 64 columns or more)
   // more than 64 rows: LDS tiles, which read the weights once per 128-256 rows
   // (us, against this kernel's tiles of 128 rows: LM head 151936 x 4096 at m =
   // 65 / 128 336 / 361 -> 248 / 271, down 4096 x 12288 28 / 32 -> 22 / 25 and 5,

@@ -213,6 +213,16 @@ def test_one_split_is_binding_at_every_m(n):
             assert L.sevo_linear_workspace_bytes(n, vocab, hidden, 1) == 0, (vocab, hidden)
 
 
+def test_linear_plan_of_a_huge_split_count():
+    """Any k_splits is planned: past one per chunk of 128 columns (64 in the
+    tiles) a larger count changes nothing."""
+    L = sevo.lib()
+    for ks in (64, 4096, 5000, 2 ** 31 - 1):
+        assert L.sevo_linear_workspace_bytes(64, 256, 4096, ks) == 32 * 64 * 256 * 4
+        assert L.sevo_linear_workspace_bytes(100, 256, 4096, ks) == 64 * 100 * 256 * 4
+        assert sevo.sevo_linear_plan(64, 256, 4096, ks)[:2] == (32, 128)
+
+
 @pytest.mark.parametrize("args", [(0, 128, 256, 0, 0), (256, 128, 256, 0, 0), (4, 96, 256, 0, 0),
                                   (4, 128, 48, 0, 0), (4, 128, 256, -1, 0), (4, 128, 256, 0, 3)])
 def test_linear_plan_rejects_bad_shapes(args):
