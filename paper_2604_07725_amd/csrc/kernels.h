@@ -136,7 +136,8 @@ struct LinearPlan {
 };
 // max_mb 4: the skinny kernel in M tiles of at most 64 rows (the other plans
 // above 64 rows may split K further, and need a larger workspace).
-// max_splits bounds a split count that the library chooses
+// k_splits 0: chosen, at most max_splits; whoever has room for the product alone
+// passes k_splits 1 (or max_splits 1)
 constexpr int kLinearMaxMb = 8, kLinearSmallMb = 4;
 LinearPlan plan_linear(int m, int n_out, int k, int k_splits, int mode,
                        int max_mb = kLinearMaxMb, int max_splits = 16);

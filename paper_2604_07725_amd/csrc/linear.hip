@@ -1,18 +1,21 @@
 // Skinny bf16 GEMM Y = X W^T on the gfx950 matrix cores, for the QKV, output,
-// gate/up and down projections and the LM head of a decode step.
+// gate/up and down projections and the LM head of a decode step of at most 64
+// candidates, and for gate/up matrices of fewer than 49152 rows up to 128; the
+// other shapes take the LDS tiles of gemm_large.hip (see plan_linear).
 //
-// At decode the batch M is the population size (<= 128 per tile), so the
-// arithmetic intensity is M flop per weight byte: far below the MFMA ridge,
-// the kernel is a weight stream and is designed for HBM bandwidth.
+// At decode the batch M is the population size, so the arithmetic intensity is
+// M flop per weight byte: far below the MFMA ridge, the kernel is a weight
+// stream and is designed for HBM bandwidth.
 //   * operands are stored fragment-major (common.h): every load of an MFMA
 //     16x16x32 operand fragment is one contiguous 1 KB read (half-line reads
 //     of row-major rows measured about a third slower);
 //   * one 256-thread workgroup per (RB row blocks of 16 weight rows, K split,
-//     M tile of up to 64 rows; 128 for the narrower gate/up matrices).  The planner picks RB and the split count so
-//     that a projection is about one round of 256 equal workgroups, one per
-//     CU (a 384-workgroup gate/up or a 192-workgroup QKV left CUs with half
-//     or double the bytes of the others); more row blocks per workgroup also
-//     share each activation fragment among more weight fragments;
+//     M tile of up to 64 rows, or 128 of a gate/up matrix of 64 MB and more).
+//     The planner picks RB and the split count so that a projection is about
+//     one round of 256 equal workgroups, one per CU (a 384-workgroup gate/up or
+//     a 192-workgroup QKV left CUs with half or double the bytes of the
+//     others); more row blocks per workgroup also share each activation
+//     fragment among more weight fragments;
 //   * the four waves take the 32-k steps of the split round-robin (wave w:
 //     steps w, w + 4, ...); at a step a wave loads RB weight fragments and
 //     the M tile's activation fragments and runs RB x MB MFMAs;

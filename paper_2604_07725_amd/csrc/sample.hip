@@ -69,7 +69,11 @@ constexpr float kLog2e = 1.4426950408889634f;
 
 // e^d for d <= 0 (or -inf) on the hardware exp2: one rounding of d log2(e),
 // then v_exp_f32 (results below 2^-126 may flush to zero; they only ever add
-// to sums whose largest term is 1)
+// to sums whose largest term is 1).  In the truncated sampler's confidence,
+// against expf: rms error to 64 bits over normal logits of deviation 0.5 / 2 / 5,
+// 64 entries 2.67 / 2.74 / 5.59e-7 (expf 2.61 / 2.73 / 5.59), 32000 6.35 / 6.48 /
+// 14.4 (6.37 / 6.63 / 14.4), 152K 7.16 / 7.28 / 16.5 (7.14 / 7.25 / 16.5): the same;
+// 128 rows of 152K 42.9 us, with expf 46.8
 __device__ __forceinline__ float exp_le0(float d) { return __builtin_amdgcn_exp2f(d * kLog2e); }
 
 __device__ __forceinline__ void lse_merge(float& m, float& s, float om, float os) {

@@ -345,7 +345,7 @@ def sevo_linear_workspace_bytes(m, n_out, k, k_splits=0) -> int:
 
 
 def sevo_linear_plan(m, n_out, k, k_splits=0, mode=LINEAR_STORE):
-    """(k splits, k per split, 16-row weight blocks per workgroup) of the skinny kernel."""
+    """(k splits, k per split, 16-row weight blocks per workgroup) of sevo_linear for m < 256."""
     plan = (C.c_int32 * 3)()
     _check(lib().sevo_linear_plan(m, n_out, k, k_splits, mode, plan))
     return tuple(int(v) for v in plan)

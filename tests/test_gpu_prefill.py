@@ -377,8 +377,8 @@ def test_prefill_confidence_full_width_reduced_depth(S):
 def test_prefill_confidence_tiny_moe_matches_oracle(S, lens, moe_chunk):
     """The tiny MoE model (2 layers, 64 experts of FFN 64, top-4) through the
     whole engine: per-row c, per-sequence C against the oracle's prefill.  The
-    expert FFN runs in one chunk or in several (the last one partial); 470
-    tokens take the decode expert kernels, 700 tokens (>= 32 entries per
+    expert FFN runs in one chunk or in several (the last one partial); 64-token
+    chunks take the decode expert kernels, 470 and 700 tokens (>= 24 entries per
     expert) the grouped large-M GEMMs, and 512 + 188 one of each; 2200 tokens
     (8800 entries) plan their lists in 1024-entry chunks (three launches).  The
     inputs have no routing choice closer than 1e-5."""
