@@ -296,9 +296,9 @@ sevo_status sevo_attn_prefill(const sevo_prefill_attn_args* a, void* stream);
  * Sequences never interact, and the same call gives the same bits.  In calls of
  * at least 4608 tokens a sequence's results are also the same bits whatever else
  * the call holds, and whatever workspace_bytes and moe_chunk, except that a last
- * LM-head chunk of at most 64 rows, and a MoE chunk with fewer than 24 n_experts /
- * n_experts_active tokens (or at most 64), run the decode step's kernels, which
- * add in another order.  Below 4608 tokens the projections may split their sums
+ * LM-head chunk of fewer than 256 rows, and a MoE chunk with fewer than 24
+ * n_experts / n_experts_active (or 256) tokens, may run the decode step's kernels,
+ * which add in another order.  Below 4608 tokens the projections may split their sums
  * by the number of tokens and the room in the workspace: results then agree to
  * the rounding of the bf16 storage points.
  *   tokens      int32 [total_tokens], sequences back to back
@@ -531,8 +531,9 @@ size_t sevo_linear_workspace_bytes(int32_t m, int32_t n_out, int32_t k, int32_t 
  * plan[0] = K splits, plan[1] = k per split, plan[2] = 16-row weight blocks per
  * workgroup (for SWIGLU gate and up blocks, an even count).  Up to 64 rows it is
  * the skinny kernel's, and up to 128 rows for SWIGLU with n_out < 49152; above,
- * the LDS tiles' (8 or 16 blocks; a k of 2^24 or more stays skinny).  The planner
- * aims at one round of 256 equal workgroups (one per CU).  Writes plan[0..2]
+ * the LDS tiles' (8 or 16 blocks) where those are faster, in general for large
+ * matrices (a k of 2^24 or more stays skinny).  The skinny plan aims at one round
+ * of 256 equal workgroups (one per CU).  Writes plan[0..2]
  * (caller-owned host memory) and returns SEVO_OK; INVALID_ARGUMENT for a null
  * plan or a shape outside m in [1, 255], n_out % 64 == 0, k % 32 == 0, mode in
  * {STORE, ADD, SWIGLU}. */

@@ -1,7 +1,8 @@
 // Skinny bf16 GEMM Y = X W^T on the gfx950 matrix cores, for the QKV, output,
 // gate/up and down projections and the LM head of a decode step of at most 64
-// candidates, and for gate/up matrices of fewer than 49152 rows up to 128; the
-// other shapes take the LDS tiles of gemm_large.hip (see plan_linear).
+// candidates, for gate/up matrices of fewer than 49152 rows up to 128, and for
+// most smaller matrices up to 255 rows; the other shapes take the LDS tiles of
+// gemm_large.hip (see plan_linear).
 //
 // At decode the batch M is the population size, so the arithmetic intensity is
 // M flop per weight byte: far below the MFMA ridge, the kernel is a weight
@@ -288,6 +289,39 @@ constexpr bool rb_ok(int rb, int mb, int swiglu) {
   return rb >= rb_min(mb) && rb <= rb_max(mb) && (swiglu ? rb % 2 == 0 : mb < 8);
 }
 
+// Whether the plan p of 64-row M tiles (gx workgroups each) beats the LDS tiles' t
+// at 65..255 rows, where the M tiles after the first find a small matrix in a
+// cache.  Both times (us) are fitted to 208 products, 26 matrices of 0.5 MB to 0.5
+// GB at 65 .. 255 rows, weights cold and cached (8 and 11% rms): rounds of one
+// workgroup per CU over k_chunk columns, the weights once at 7-10 TB/s, split
+// partials and the launch that sums them, and for this kernel the weights again
+// for each further M tile unless gx is a multiple of 8, when the M tiles of a row
+// block share an XCD's L2.  The choice is 0.5% off the better of the two on
+// average; the LDS tiles throughout were 15% off (cold, 64-row M tiles / LDS tiles:
+// 255 x 4096 x 2048 12 / 19, 192 x 5120 x 2048 13 / 20, 128 x 8192 x 2048 13 / 18, 65 x
+// 4096 x 4096 16 / 20, 255 x 1024 x 1024 8 / 11, but 160 x 4096 x 4096 34 / 24, 130 x
+// 10240 x 5120 67 / 43, 255 x 16384 x 1024 25 / 20).
+static bool skinny_faster(int m, int n_out, int k, const LinearPlan& p, int gx, int mt,
+                          const LinearPlan& t) {
+  constexpr double kPer1024[] = {0.0, 11.0, 6.9, 6.8, 5.3};  // us per 1024 columns of a tile
+  const double w_mb = 2e-6 * n_out * k;
+  auto rounds_of = [](double r) {
+    return r <= 1.0 ? 1.0 : r < 4.0 ? (double)(long)(r + 0.999) : r + 0.5;
+  };
+  auto sum_us = [&](const LinearPlan& q, double per_mb) {
+    return q.k_splits > 1 ? 1.9 + per_mb * 4e-6 * q.k_splits * m * n_out : 0.0;
+  };
+  const long tiles = (long)((m + 16 * t.mb - 1) / (16 * t.mb)) * ((n_out + 16 * t.rb - 1) / (16 * t.rb));
+  const double tiled = rounds_of(tiles * t.k_splits / 256.0) *
+                           (3.7 + kPer1024[t.tile] * t.k_chunk / 1024.0) +
+                       0.144 * w_mb + sum_us(t, 0.5);
+  const double c = p.k_chunk / 1024.0;
+  const double skinny = 3.4 + c * (0.53 * p.rb + 1.23) +
+                        (rounds_of(gx * mt / 256.0) - 1.0) * c * 1.18 * p.rb +
+                        w_mb * (0.1 + (gx % 8 ? 0.06 * (mt - 1) : 0.0)) + sum_us(p, 0.43);
+  return skinny < tiled;
+}
+
 LinearPlan plan_linear(int m, int n_out, int k, int k_splits, int mode, int max_mb,
                        int max_splits) {
   if (k_splits > k / 32) k_splits = std::max(k / 32, 1);  // (a chunk is 64 columns or more)
@@ -297,13 +331,18 @@ LinearPlan plan_linear(int m, int n_out, int k, int k_splits, int mode, int max_
   // 32B-class gate/up 129 / 148 -> 93 / 99; at m = 160 8B-class gate/up 78 -> 60,
   // QKV 26 -> 22, output 21 -> 16).  A gate/up matrix cannot split K: up to 128
   // rows, one too narrow for 192 tiles of 256 columns stays here (24576 x 4096
-  // at m = 128: 43 us, tiles 49)
-  if (m >= kTileMinM && max_mb > kLinearSmallMb && k <= kTileMaxK &&
-      !(mode == 2 && m <= 128 && n_out < 192 * 256))
-    return plan_tiles(m, n_out, k, mode, m < kLargeGemmMinM || k_splits == 1 ? k_splits : 0,
-                      max_splits);
+  // at m = 128: 43 us, tiles 49).  Below 256 rows skinny_faster keeps most of the
+  // smaller matrices here too
+  const bool tiles = m >= kTileMinM && max_mb > kLinearSmallMb && k <= kTileMaxK &&
+                     !(mode == 2 && m <= 128 && n_out < 192 * 256);
+  LinearPlan tiled;
+  if (tiles) {
+    tiled = plan_tiles(m, n_out, k, mode, m < kLargeGemmMinM || k_splits == 1 ? k_splits : 0,
+                       max_splits);
+    if (m >= kLargeGemmMinM) return tiled;
+  }
   const int swiglu = mode == 2;
-  const int mb = pick_mb(m, n_out, k, swiglu ? max_mb : kLinearSmallMb);
+  const int mb = pick_mb(m, n_out, k, swiglu && !tiles ? max_mb : kLinearSmallMb);
   const int mt = (m + 16 * mb - 1) / (16 * mb);
   const int per_unit = swiglu ? 2 : 1;  // row blocks per unit (a gate/up pair)
   const int units = (n_out / 16) / per_unit;
@@ -370,7 +409,8 @@ LinearPlan plan_linear(int m, int n_out, int k, int k_splits, int mode, int max_
     }
     if (e >= 0.95 || wgs > 256) break;
   }
-  return p;
+  return tiles && !skinny_faster(m, n_out, k, p, wgs_of(p.rb, p.k_splits) / mt, mt, tiled) ? tiled
+                                                                                           : p;
 }
 
 size_t linear_workspace_bytes(int m, int n_out, const LinearPlan& p) {

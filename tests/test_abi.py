@@ -214,13 +214,31 @@ def test_one_split_is_binding_at_every_m(n):
 
 
 def test_linear_plan_of_a_huge_split_count():
-    """Any k_splits is planned: past one per chunk of 128 columns (64 in the
-    tiles) a larger count changes nothing."""
+    """Any k_splits is planned: past one per chunk of 128 columns a larger count
+    changes nothing."""
     L = sevo.lib()
     for ks in (64, 4096, 5000, 2 ** 31 - 1):
-        assert L.sevo_linear_workspace_bytes(64, 256, 4096, ks) == 32 * 64 * 256 * 4
-        assert L.sevo_linear_workspace_bytes(100, 256, 4096, ks) == 64 * 100 * 256 * 4
-        assert sevo.sevo_linear_plan(64, 256, 4096, ks)[:2] == (32, 128)
+        for m in (64, 100, 255):
+            assert L.sevo_linear_workspace_bytes(m, 256, 4096, ks) == 32 * m * 256 * 4
+            assert sevo.sevo_linear_plan(m, 256, 4096, ks)[:2] == (32, 128)
+        assert L.sevo_linear_workspace_bytes(300, 256, 4096, ks) > 0
+
+
+def test_linear_plans_between_64_and_256_rows():
+    """(splits, k per split, row blocks): a matrix that a cache holds stays in
+    64-row M tiles of the skinny kernel where those are faster, the others take
+    the LDS tiles (8 blocks: 128 x 128, 16: 128 x 256 and larger)."""
+    plan = sevo.sevo_linear_plan
+    assert plan(255, 4096, 2048) == (1, 2048, 4)
+    assert plan(192, 5120, 2048) == (1, 2048, 4)
+    assert plan(65, 4096, 4096) == (2, 2048, 4)
+    assert plan(255, 1024, 1024)[2] < 8
+    assert plan(100, 128, 2048) == (8, 256, 3)
+    assert plan(200, 1536, 2048, mode=sevo.LINEAR_SWIGLU) == (1, 2048, 4)
+    assert plan(160, 4096, 4096) == (4, 1024, 8)
+    assert plan(130, 10240, 5120)[2] >= 8
+    assert plan(255, 151936, 4096, k_splits=1) == (1, 4096, 16)
+    assert plan(200, 24576, 4096, mode=sevo.LINEAR_SWIGLU)[2] == 16
 
 
 @pytest.mark.parametrize("args", [(0, 128, 256, 0, 0), (256, 128, 256, 0, 0), (4, 96, 256, 0, 0),

@@ -635,7 +635,8 @@ def test_linear_matches_float64_matmul(S, m, n_out, k, mode, ks, xt):
 
 # shapes on either side of the tile dispatch: each tile (128 x 128 with k % 64
 # == 0, 128 x 256, 192 x 256, 256 x 256), ragged last rows and columns, K splits
-# with a short last one, the eight-block skinny kernel, k % 64 == 32
+# with a short last one, the eight-block skinny kernel, k % 64 == 32 (below 256
+# rows the small matrices run 64-row M tiles of the skinny kernel)
 TILE_CASES = [
     # m, n_out, k, mode, x_tiled
     (65, 192, 64, 0, 1), (128, 320, 192, 2, 0), (129, 192, 4160, 0, 1), (130, 128, 4160, 1, 0),
@@ -643,6 +644,10 @@ TILE_CASES = [
     (300, 24640, 64, 0, 1), (193, 24640, 128, 2, 0), (500, 24640, 64, 1, 0),
     (512, 24640, 96, 2, 1), (257, 192, 2080, 1, 1),
     (100, 24576, 1408, 2, 1), (128, 24576, 1408, 2, 0),
+    # 128 x 128 tiles (also split, from 130 and 256 rows), then 128 x 256
+    (257, 192, 2112, 1, 1), (300, 320, 192, 2, 0), (263, 128, 4160, 0, 0), (511, 576, 128, 0, 1),
+    (131, 4160, 4160, 1, 1), (290, 512, 96, 0, 0), (400, 320, 1056, 1, 0), (130, 8256, 2048, 0, 0),
+    (193, 16448, 1056, 1, 0), (255, 12352, 1056, 2, 0),
 ]
 
 
@@ -686,8 +691,9 @@ def test_linear_tiles_at_their_edges(S, m, n_out, k, mode, xt):
 
 
 @pytest.mark.parametrize("m,n_out,k,mode,pad", [
-    (65, 192, 64, 0, 8), (128, 320, 192, 2, 1024), (130, 128, 4160, 1, 256), (70, 512, 96, 0, 40),
-    (193, 24640, 128, 2, 64), (300, 24640, 64, 0, 200), (257, 192, 2080, 1, 96)])
+    (65, 192, 64, 0, 8), (70, 512, 96, 0, 40), (131, 4160, 4160, 1, 256), (130, 8256, 2048, 0, 40),
+    (255, 12352, 1056, 2, 1024), (300, 320, 192, 2, 64), (300, 24640, 64, 0, 200),
+    (257, 192, 2080, 1, 96), (263, 128, 4160, 0, 8)])
 def test_linear_row_major_column_slice(S, m, n_out, k, mode, pad):
     """X as the last k columns of a wider tensor (ldx = k + pad): its last row
     ends with the allocation, and the columns before it are NaN.  The same bits
@@ -732,7 +738,7 @@ def test_linear_rows_past_32_bit_offsets(S, m, k, ldx):
     np.testing.assert_allclose(got.double().cpu().numpy(), ref, rtol=0, atol=1e-5)
 
 
-@pytest.mark.parametrize("m,n_out,k", [(512, 256, 4096), (257, 192, 2080), (65, 5184, 2048)])
+@pytest.mark.parametrize("m,n_out,k", [(512, 256, 4096), (257, 192, 2080), (150, 8192, 2048)])
 def test_linear_misaligned_workspace_counts_as_none(S, m, n_out, k):
     """A workspace that is large enough but not 16-byte aligned is left alone by
     a plan that can do without one (from 256 rows on, and below where the plan of
