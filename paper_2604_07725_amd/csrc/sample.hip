@@ -367,10 +367,10 @@ __device__ __forceinline__ float2 lse16(const float (&x)[16], float t) {
 // confidence over 152K logits, us, carried / per tile: 1121 rows 163 / 169, 1927
 // 266 / 266, 4096 513 / 504).
 constexpr int kMaxTiles = kWave;
-template <bool RAW>
+template <bool RAW, int MAX = kMaxTiles>
 struct TileSums {
-  float2 z[kMaxTiles][4];
-  float2 raw[RAW ? kMaxTiles : 1][4];
+  float2 z[MAX][4];
+  float2 raw[RAW ? MAX : 1][4];
   float best[4];
   int idx[4];
 
@@ -405,7 +405,8 @@ struct TileSums {
 };
 
 // Pass 1.  MODE 0: T = 0 (greedy, no noise, z = x); 1: T = 1 (z = x); 2: any
-// other T (z = x / T).  CONF: also the chunk's conf_k largest raw logits.
+// other T (z = x / T).  CONF: also the chunk's conf_k largest raw logits (only
+// then a chunk may be several tiles).
 template <int MODE, bool CONF>
 __global__ __launch_bounds__(256) void sample_partial_kernel(
     const float* __restrict__ logits, int vocab, int64_t ld, int row_tiles, int tiles, float temp,
@@ -414,13 +415,14 @@ __global__ __launch_bounds__(256) void sample_partial_kernel(
   // for MODE 2 with the confidence also the statistics of the raw logits
   // (T = 1), else they are z's
   constexpr bool kRaw = MODE == 2 && CONF;
-  __shared__ TileSums<kRaw> sums;
+  __shared__ TileSums<kRaw, CONF ? kMaxTiles : 1> sums;
   __shared__ float wtop[4][kConfMaxK];
   __shared__ float cand[4][kWave];
   const int chunk = blockIdx.x;
   const int i = blockIdx.y;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const float* row = logits + (size_t)i * ld;
+  if constexpr (!CONF) tiles = 1;
   uint64_t cu = 0;
   uint32_t pos = 0;
   if constexpr (MODE != 0) {
@@ -732,16 +734,20 @@ __global__ __launch_bounds__(256) void sample_trunc_final_kernel(
   }
 }
 
-// 4096-entry tiles per workgroup.  A wave's list admits about conf_k / t of
-// tile t's entries and is sorted and merged once per chunk, so with enough
-// rows chunks are long: as many tiles as leave kTiledGroups workgroups, in equal
-// chunks (1121 scored rows x 152K logits, greedy with the confidence: 250 us
-// with four tiles, 185 with nineteen).  Below four tiles each the longer chunks
-// only idle CUs (64 rows at T = 1: 31 us with one tile, 49 with two).
-constexpr int kTiledGroups = 2048;
+// 4096-entry tiles per workgroup of a list pass.  A wave's list admits about
+// conf_k / t of tile t's entries and is sorted and merged once per chunk, so with
+// enough rows chunks are long: as many tiles as leave kTiledGroups workgroups, in
+// equal chunks.  Fewer than kLongChunkTiles tiles in all, and every pass without
+// lists, run one tile each: a tile's loads then overlap other workgroups' work
+// instead of waiting for their own (us, one tile / long chunks, greedy with the
+// confidence, T = 0.7 with it, top-k 20: 256 rows of 152K 52 / 69, 108 / 137, 71 /
+// 101; 512 rows 95 / 99, 203 / 222, 131 / 133; 1024 rows 177 / 161, 392 / 377, 247 /
+// 193; 4096 rows of 32000 165 / 165, 347 / 341, 226 / 201; without lists 256 rows
+// greedy 30 / 45, 2048 rows 212 / 252).
+constexpr int kTiledGroups = 2048, kLongChunkTiles = 24576;
 static int row_tiles_of(int vocab) { return (vocab + kSampleChunk - 1) / kSampleChunk; }
 static int sample_tiles(int n, int row_tiles) {
-  if ((long long)n * row_tiles < 4 * kTiledGroups) return 1;
+  if ((long long)n * row_tiles < kLongChunkTiles) return 1;
   const int chunks = std::max(std::min(row_tiles, (kTiledGroups + n - 1) / n),
                               (row_tiles + kMaxTiles - 1) / kMaxTiles);
   return (row_tiles + chunks - 1) / chunks;
@@ -772,7 +778,8 @@ hipError_t launch_logprob_sample(const float* logits, int n, int vocab, int64_t 
                                  int conf_k, float* out_conf, float* conf_sum, hipStream_t st,
                                  int top_k, float top_p, float min_p) {
   if (n == 0) return hipSuccess;
-  const int row_tiles = row_tiles_of(vocab), tiles = sample_tiles(n, row_tiles);
+  const int row_tiles = row_tiles_of(vocab);
+  const int tiles = conf_k > 0 || top_k > 0 ? sample_tiles(n, row_tiles) : 1;
   const int nchunks = (row_tiles + tiles - 1) / tiles;
   SamplePartial* part = reinterpret_cast<SamplePartial*>(workspace);  // per tile
   char* lists = reinterpret_cast<char*>(workspace) + partial_bytes(n, row_tiles);

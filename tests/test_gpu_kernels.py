@@ -490,14 +490,16 @@ def test_sampler_at_the_largest_vocabulary(S, temp):
     assert abs(lps.item()) <= 4e-6     # two roundings at 40
 
 
-@pytest.mark.parametrize("temp,top_k,conf", [(0.0, 0, 20), (1.0, 0, 0), (0.7, 0, 20), (0.7, 20, 20)])
-def test_sampler_rows_do_not_depend_on_the_batch(S, temp, top_k, conf):
-    """1200 rows of 152K logits, whose workgroups walk many tiles each, against
-    the first and last 30 of them alone (one tile each): the same ids,
-    log-probabilities and confidences, bit for bit."""
+@pytest.mark.parametrize("n,vocab,temp,top_k,conf", [
+    (1200, 151936, 0.0, 0, 20), (1200, 151936, 1.0, 0, 0), (1200, 151936, 0.7, 0, 20),
+    (1200, 151936, 0.7, 20, 20), (2050, 266240, 0.0, 0, 20)])
+def test_sampler_rows_do_not_depend_on_the_batch(S, n, vocab, temp, top_k, conf):
+    """Many rows, whose workgroups walk many tiles each where they keep lists (the
+    last case would put a row's 65 tiles in one chunk, past the 64 a chunk can
+    be), against the first and last 30 of them alone (one tile each): the same
+    ids, log-probabilities and confidences, bit for bit."""
     sevo, _ = S
-    n, vocab = 1200, 151936
-    say(f"sampler batch invariance T={temp} top_k={top_k} conf={conf}")
+    say(f"sampler batch invariance {n}x{vocab} T={temp} top_k={top_k} conf={conf}")
     g = torch.Generator(device="cuda").manual_seed(3)
     x = torch.randn(n, vocab, device="cuda", generator=g) * 2.0
     uid = torch.arange(n, dtype=torch.int64, device="cuda") * 977 + 1
